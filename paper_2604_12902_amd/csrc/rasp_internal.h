@@ -66,6 +66,8 @@ struct QueueState {
     unsigned long long misfits;        // hot-cell first pass: survivors whose hot cells do not all fit
     unsigned long long head_m;         // next unclaimed misfit
     unsigned long long pad2[2];
+    unsigned long long count[8];       // traces: machines in each list,
+    unsigned long long next[8];        // and the next unclaimed one
 };
 
 // Hot-cell tables.  A first pass profiles the last R transitions of every
@@ -87,6 +89,41 @@ struct HotArgs {
     uint16_t *tags;
     uint32_t *mis;                     // misfit list
 };
+
+// Lists of machines (index in the launch, transitions to go) behind a first
+// pass: what the trace kernel does with its survivors.
+enum : uint32_t {
+    kListFirst = 0,                    // the first pass's survivors (count in survivors)
+    kListMisfit = 1,                   // a hot-cell first pass's misfits (count in misfits)
+    kListWarm = 2,                     // survivors of a second pass, where the first was short
+    kListGeneral = 3,                  // not for nodes: k_whole, or the work queue if they are many
+    kListFull = 4,                     // need larger tables
+    kListLast = 5,                     // as kListGeneral, of the machines with larger tables
+    kListEnd = 6,                      // near the end of their budget
+    kListDone = 7,                     // (no list: finished)
+    kLists = 8
+};
+struct TraceArgs {
+    uint32_t NO, ND;                   // nodes and data words a lane
+    uint32_t in;                       // the list this launch works on
+    uint32_t few;                      // k_whole: the longest list it takes
+    uint32_t *idx[7], *left[7];        // by list (left null: the budget less the first pass)
+};
+constexpr uint32_t kTraceMax = 8;      // transitions of a node at most
+constexpr uint32_t kTraceRounds = 16;  // general steps of a lane between runs of macro steps
+constexpr uint32_t kTraceNear = 32;    // macro steps before its end from which a lane waits for others,
+constexpr uint32_t kTraceEnd = 1;      // and from which its machine leaves
+constexpr uint32_t kTraceEvents = 24;  // general steps (and one in 2,048 transitions) before a machine leaves
+constexpr uint32_t kTraceFulls = 2;    // times its tables are full (and once in 1,024) before it leaves
+constexpr uint32_t kTraceNodes = 16, kTraceData = 10;        // 7 waves a CU
+constexpr uint32_t kTraceNodes2 = 48, kTraceData2 = 40;      // 2 waves a CU
+// The largest memory traces are compiled for.  Positions would do to 2^15, but
+// a program that sweeps a large array computes addresses anew on every round
+// and ends up on the general lists, without a slot in LDS there (rollouts,
+// n = 2,048: 159 ms with traces, 144 without).
+constexpr uint32_t kTraceMaxN = 1u << 10;
+constexpr uint32_t trace_lds_bytes(uint32_t NO, uint32_t ND) { return NO * (1024u + 128u) + (ND + 2u) * 256u + ND * 128u; }
+constexpr uint32_t whole_lds_bytes(uint32_t max_n, uint32_t sh) { return (max_n + 2u) << (sh + 2u); }
 
 // Descriptor-check error bits.
 enum : uint32_t {
@@ -133,9 +170,19 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
                              uint32_t already, uint32_t isa, bool pow2, bool wm, uint32_t epoch,
                              uint32_t lds_words, uint32_t max_n, uint32_t max_ell,
                              uint32_t waves_per_block, uint32_t blocks, uint32_t cap, uint32_t *surv,
-                             QueueState *q, hipStream_t st, bool misfits = false);
-// (misfits: the work list is a hot-cell first pass's misfit list, counted by
-// q->misfits and claimed through q->head_m)
+                             QueueState *q, hipStream_t st, uint32_t which = 0,
+                             const uint32_t *rest_left = nullptr, uint32_t few = 0);
+// (which 1: the work list is a hot-cell first pass's misfit list, counted by
+// q->misfits and claimed through q->head_m; kListGeneral, kListEnd: that
+// list, rest_left its machines' transitions to go; a list of at most `few`
+// machines is left alone)
+// the trace kernel over list ta.in
+// whole memories in LDS, 2^sh lanes a wave, over list ta.in if it has at
+// most ta.few machines
+hipError_t launch_whole(const BatchTable *tab, uint32_t isa, bool pow2, bool wm, const TraceArgs &ta, uint32_t sh,
+                        uint32_t max_n, uint32_t blocks, QueueState *q, hipStream_t st);
+hipError_t launch_trace(const BatchTable *tab, uint32_t already, uint32_t isa, bool wm, const TraceArgs &ta,
+                        uint32_t blocks, QueueState *q, hipStream_t st);
 // the persistent kernel over the fits of a hot-cell first pass, each
 // machine's hot cells in its lane's LDS table
 hipError_t launch_persistent_hot(const BatchTable *tab, const uint32_t *work, uint32_t already, uint32_t isa,

@@ -91,6 +91,12 @@ typedef __attribute__((address_space(1))) int32_t gi32;
 typedef __attribute__((address_space(1))) uint64_t gu64;
 __device__ __forceinline__ gi32 *gptr(int32_t *p) { return (gi32 *)p; }
 __device__ __forceinline__ const gi32 *gptr(const int32_t *p) { return (const gi32 *)p; }
+// the same for a batch's state arrays
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T *gany(T *p)
+{
+    return (__attribute__((address_space(1))) T *)p;
+}
 
 // The next instruction's two words from HBM: one 8-byte load of the cell
 // holding word np (memory slices are padded to a multiple of 4 words, so the
@@ -388,6 +394,13 @@ struct HotMem {
         j = ld(nq);
     }
 };
+
+// LDS by byte address (no kernel here has LDS but its dynamic block, which
+// then starts at 0: an address needs no base added)
+typedef __attribute__((address_space(3))) int32_t li32;
+typedef __attribute__((address_space(3))) uint16_t lu16;
+__device__ __forceinline__ li32 &lds_i32(uint32_t byte) { return *reinterpret_cast<li32 *>(byte); }
+__device__ __forceinline__ lu16 &lds_u16(uint32_t byte) { return *reinterpret_cast<lu16 *>(byte); }
 
 // input tape: in HBM, or staged in the lane's LDS slot
 struct TapeG {
@@ -1272,7 +1285,8 @@ hipError_t launch_plain(const BatchTable *tab, uint64_t total, uint32_t cap, uin
 // (or 16-byte store) moves a word (four words) of every lane that has one to
 // move; only machines that stored into LDS (or are new) are written back.
 // Work item k is machine work[k] of the launch (or machine k when work is
-// null); machines have already applied `already` transitions this run.
+// null); machines have already applied `already` transitions this run (with
+// rest_left, item k has rest_left[k] transitions to go instead).
 // With surv non-null the launch is a first pass: a machine runs at most `cap`
 // transitions, and one still running after them is written back and appended
 // to surv (its index in the launch) for a later launch.
@@ -1283,6 +1297,7 @@ hipError_t launch_plain(const BatchTable *tab, uint64_t total, uint32_t cap, uin
 // four words as one 16-byte access; global and LDS views of it
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4i gv4i;
+typedef __attribute__((address_space(3))) v4i lv4i;
 // direct global-to-LDS load: lane l's 4 bytes from g land at LDS word row +
 // l; row is the same for every lane of the wave
 typedef __attribute__((address_space(1))) void gv;
@@ -1313,7 +1328,8 @@ __device__ __forceinline__ void persistent_body(const BatchTable *__restrict__ t
                                                 const uint32_t *__restrict__ work, uint32_t already,
                                                 uint32_t epoch, uint32_t P, uint32_t TL, uint32_t wm,
                                                 uint32_t cap, uint32_t *__restrict__ surv,
-                                                QueueState *__restrict__ q, uint32_t which)
+                                                QueueState *__restrict__ q, uint32_t which,
+                                                const uint32_t *__restrict__ rest_left, uint32_t few)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wib = threadIdx.x / kWave;
@@ -1321,10 +1337,11 @@ __device__ __forceinline__ void persistent_body(const BatchTable *__restrict__ t
     const uint32_t SP = P + 4u + (TLDS ? TL : 0u);         // slot: memory, spares, tape
     const uint32_t wave_base = wib * kWave * SP;           // LDS word index of the wave's slots
     const uint32_t slot = wave_base + lane;                 // this lane's slot word 0 (word k at + 64 k)
-    // the survivor (or misfit) count written by the first pass, and the
-    // list's claim counter
-    if (work != nullptr) total = which ? q->misfits : q->survivors;
-    unsigned long long *const head = which ? &q->head_m : &q->head;
+    // the count of the list (survivors and misfits written by the first pass,
+    // the rest by the trace kernel), and its claim counter
+    if (work != nullptr) total = which == kListFirst ? q->survivors : which == 1 ? q->misfits : q->count[which];
+    unsigned long long *const head = which == kListFirst ? &q->head : which == 1 ? &q->head_m : &q->next[which];
+    if (few != 0 && total <= few) return;                  // few enough for k_whole
 
     bool has = false, exhausted = false, fresh = false, cut = false;
     Regs r{};
@@ -1382,7 +1399,7 @@ __device__ __forceinline__ void persistent_body(const BatchTable *__restrict__ t
                         Y = bp->Y + bp->y_off[v];
                         gid = static_cast<uint32_t>(g);
                         done = 0;
-                        limit = budget - already;
+                        limit = rest_left ? rest_left[item] : budget - already;
                         cut = cap < limit;
                         if (cut) limit = cap;
                         has = true;
@@ -1539,8 +1556,10 @@ __device__ __forceinline__ void persistent_body(const BatchTable *__restrict__ t
             if (sm) {
                 const int leader = __ffsll(static_cast<unsigned long long>(sm)) - 1;
                 unsigned long long base = 0;
+                // (a pass over a survivor list has a list of its own)
+                unsigned long long *const count = work ? &q->count[kListWarm] : &q->survivors;
                 if (lane == static_cast<uint32_t>(leader))
-                    base = atomicAdd(&q->survivors, static_cast<unsigned long long>(__popcll(sm)));
+                    base = atomicAdd(count, static_cast<unsigned long long>(__popcll(sm)));
                 base = __shfl(base, leader);
                 if (survive) surv[base + __popcll(sm & ((1ull << lane) - 1ull))] = gid;
             }
@@ -1556,12 +1575,13 @@ __global__ __launch_bounds__(256) void k_persistent(const BatchTable *__restrict
                                                     uint32_t already, uint32_t epoch,
                                                     uint32_t P, uint32_t TL, uint32_t wm,
                                                     uint32_t cap, uint32_t *__restrict__ surv,
-                                                    QueueState *__restrict__ q, uint32_t which)
+                                                    QueueState *__restrict__ q, uint32_t which,
+                                                    const uint32_t *__restrict__ rest_left, uint32_t few)
 {
     if (tab->count == 1)
-        persistent_body<ISA, MODE, POW2, TLDS, true>(tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which);
+        persistent_body<ISA, MODE, POW2, TLDS, true>(tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few);
     else
-        persistent_body<ISA, MODE, POW2, TLDS, false>(tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which);
+        persistent_body<ISA, MODE, POW2, TLDS, false>(tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few);
 }
 
 // ---------------------------------------------------------------------------
@@ -1749,14 +1769,807 @@ hipError_t launch_persistent_hot(const BatchTable *tab, const uint32_t *work, ui
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// K3 by traces: the survivors of a first pass run as short straight-line
+// macro steps that the lane holding a machine compiles for it.
+//
+// A long runner spends its budget in a loop over a handful of instructions
+// and data words (uneven: 2-12 instructions and at most 10 data words for 95%
+// of the machines that run to the budget; fig1: at most 15 nodes and 11 words
+// for 99%), and stepping it one transition at a time decodes the same
+// instructions again on every round.  Here a lane keeps a small graph of
+// nodes in LDS.  A node stands for up to kTraceMax transitions from one value
+// of i on, which together do
+//     a' = (keep ? a : 0) + imm (+ or - M[A], or * M[A]);  M[S] = a';
+//     next = test(a') ? taken : fall
+// -- LOAD, then ADD / SUB (MUL), then STORE, then a conditional jump, each at
+// most once and any of them missing (a LOAD drops what the accumulator held;
+// JMP, a PRINT past the output capacity and a jump on a just-loaded constant
+// cost nothing) -- 2.6 to 3.4 transitions a node over the synthetic
+// populations.  The words A and S name live in the lane's LDS words; all
+// others stay in HBM.  Every lane of the wave executes its own node at every
+// macro step: three LDS reads (its data word and both successors' records)
+// and one store, some twenty vector instructions and no test that can leave
+// the loop.  What is not compiled yet is a stub, a node that keeps the
+// machine where it is; the wave looks for lanes on stubs every T macro steps
+// and compiles, or steps a transition in general, for those that need it.
+//
+// The code a node was compiled from may not change under it.  A 64-bit set
+// (bit (word / 2) mod 64) covers the words of all compiled instructions.  A
+// STORE to a word in the set that leaves the word as it is (most of them) is
+// a node of its own that tests just that; one that changes the word drops
+// the nodes, and the word is a data word from then on, whose LOADs read it as
+// data and whose other instructions step in general.
+//
+// A machine that steps in general too often (uneven: 0.8% of the survivors,
+// plain-scale 4%: jumps and addresses computed anew on every round) leaves
+// for k_whole, one whose tables are too small (uneven 2%, fig1 1%) for a
+// launch with larger ones, and one near the end of its budget for the work
+// queue, which takes its last few transitions at full occupancy.
+// The bound is a macro step's LDS round trip and the chain behind it (about
+// 140 cycles) and, with several waves a SIMD, the issue of its instructions;
+// LDS decides how many waves there are.
+// ---------------------------------------------------------------------------
+
+constexpr uint32_t kNone = ~0u;
+
+// what a node without transitions stands for
+enum : uint32_t {
+    kStub = 0,                           // not compiled yet
+    kTrap = 1,                           // a jump onto itself: a fixed point
+    kMiss = 2,                           // a STORE that would change a word nodes rest on
+    kKept = 3                            // behind a STORE that left such a word as it was: a is that word
+};
+
+// A lane's nodes and data words in LDS.  Record x of the lane is the 16 bytes
+// at nb + 1024 x:
+//   x  imm (one more when the data word is subtracted: v ^ -1 = -v - 1)
+//   y  LDS word of A << 16 | transitions k (0: a stub)
+//   z  LDS word of S << 16 | test a' != 0 instead of a' > 0 << 13 | kind << 11 |
+//      own number << 3 | not found by i << 2 | sub (mul in the word set) << 1 | keep
+//   w  high half of the node's i << 16 | taken << 8 | fall, nodes as 1 KiB
+//      blocks of LDS
+// (a wave's nodes start on a 1 KiB boundary).  key x: the low half of its i.
+// Data word d is at db + 256 d; word ND is always 0 (no A), word ND + 1 takes
+// the stores of nodes without one.  pos d: the memory position it holds, bit
+// 15 set once it may differ from HBM.  Every array is interleaved across the
+// lanes of the wave.
+struct TraceTab {
+    uint32_t nb, db, kb, pb;
+    uint32_t NO, ND;
+    uint32_t nn, dn;
+    uint64_t code;                       // words of compiled instructions
+    uint64_t keys, held, dirty;          // nodes' i, data words' positions, those stored to
+    uint32_t ev, full;                   // general steps and nodes dropped; full tables emptied
+    gi32 *M;
+
+    __device__ __forceinline__ uint32_t node(uint32_t x) const { return nb + (x << 10); }
+    __device__ __forceinline__ uint32_t data(uint32_t d) const { return db + (d << 8); }
+    __device__ __forceinline__ lu16 &key(uint32_t x) const { return lds_u16(kb + (x << 7)); }
+    __device__ __forceinline__ lu16 &pos(uint32_t d) const { return lds_u16(pb + (d << 7)); }
+    __device__ __forceinline__ static uint64_t bit(uint32_t p) { return 1ull << ((p >> 1) & 63u); }
+    __device__ __forceinline__ uint32_t transitions(uint32_t x) const
+    {
+        return static_cast<uint32_t>(lds_i32(node(x) + 4u)) & 0xffffu;
+    }
+    __device__ __forceinline__ uint32_t kind(uint32_t x) const
+    {
+        return (static_cast<uint32_t>(lds_i32(node(x) + 8u)) >> 11) & 3u;
+    }
+    __device__ __forceinline__ int32_t at(uint32_t x) const
+    {
+        return static_cast<int32_t>((static_cast<uint32_t>(lds_i32(node(x) + 12u)) & 0xffff0000u) | key(x));
+    }
+    // the node at i
+    __device__ __forceinline__ uint32_t find(int32_t i) const
+    {
+        if ((keys & bit(static_cast<uint32_t>(i))) == 0) return kNone;
+        uint64_t m = 0;
+#pragma unroll 4
+        for (uint32_t x = 0; x < nn; ++x)
+            m |= static_cast<uint64_t>(key(x) == (static_cast<uint32_t>(i) & 0xffffu)) << x;
+        while (m != 0) {
+            const uint32_t x = static_cast<uint32_t>(__builtin_ctzll(m));
+            m &= m - 1ull;
+            if (at(x) == i && (lds_i32(node(x) + 8u) & 4) == 0) return x;
+        }
+        return kNone;
+    }
+    // the data word at position p
+    __device__ __forceinline__ uint32_t dfind(uint32_t p) const
+    {
+        uint32_t f = kNone;
+        if ((held & bit(p)) == 0) return f;
+#pragma unroll 4
+        for (uint32_t d = 0; d < dn; ++d) f = (pos(d) & 0x7fffu) == p ? d : f;
+        return f;
+    }
+    __device__ __forceinline__ bool stored(uint32_t p) const
+    {
+        bool f = false;
+        if ((dirty & bit(p)) == 0) return f;
+#pragma unroll 4
+        for (uint32_t d = 0; d < dn; ++d) f |= pos(d) == (p | 0x8000u);
+        return f;
+    }
+    __device__ __forceinline__ void drop_nodes() { nn = 0; code = keys = 0; }
+    // stored words back to HBM
+    __device__ __forceinline__ void write_back()
+    {
+        for (uint32_t d = 0; d < dn; ++d) {
+            const uint32_t p = pos(d);
+            if (p & 0x8000u) M[p & 0x7fffu] = lds_i32(data(d));
+        }
+        dn = 0;
+        held = dirty = 0;
+    }
+    // a node without transitions (kinds other than kStub are not found by i)
+    __device__ __forceinline__ uint32_t stub(int32_t i, uint32_t kd)
+    {
+        const uint32_t x = nn++, self = node(x) >> 10, ui = static_cast<uint32_t>(i);
+        if (kd == kStub) keys |= bit(ui);
+        li32 *const rec = &lds_i32(node(x));
+        rec[0] = 0;
+        rec[1] = static_cast<int32_t>(data(ND) << 14);
+        rec[2] = static_cast<int32_t>((data(ND + 1u) << 14) | (kd << 11) | (x << 3) | (kd != kStub ? 4u : 0u) | 1u);
+        rec[3] = static_cast<int32_t>((ui & 0xffff0000u) | (self << 8) | self);
+        key(x) = static_cast<uint16_t>(ui & 0xffffu);
+        return x;
+    }
+    // a data word for position p (dn < ND)
+    __device__ __forceinline__ uint32_t add(uint32_t p)
+    {
+        lds_i32(data(dn)) = M[p];
+        pos(dn) = static_cast<uint16_t>(p);
+        held |= bit(p);
+        return dn++;
+    }
+    // data word d (position p) may differ from HBM from now on
+    __device__ __forceinline__ void soil(uint32_t d, uint32_t p)
+    {
+        pos(d) = static_cast<uint16_t>(p | 0x8000u);
+        dirty |= bit(p);
+    }
+    __device__ __forceinline__ int32_t ld(uint32_t p) const
+    {
+        const uint32_t d = dfind(p);
+        int32_t v;
+        if (d != kNone) v = lds_i32(data(d)); else v = M[p];
+        return v;
+    }
+    // a store outside the nodes; if it changes a word they rest on they go,
+    // and the word becomes a data word
+    __device__ __forceinline__ void st(uint32_t p, int32_t v)
+    {
+        uint32_t d = dfind(p);
+        const bool was = d != kNone && (pos(d) & 0x8000u) != 0;
+        if (!was && (code & bit(p)) != 0) {
+            if (M[p] == v) return;
+            ev += nn;
+            drop_nodes();
+            if (d == kNone && dn < ND) d = add(p);
+        }
+        if (d != kNone) {
+            lds_i32(data(d)) = v;
+            soil(d, p);
+        } else {
+            M[p] = v;
+        }
+    }
+    // the word a STORE at i writes to
+    __device__ __forceinline__ uint32_t target(int32_t i, uint32_t n) const
+    {
+        const uint32_t p = cmod(i, n);
+        return cmod(M[p + 1u == n ? 0u : p + 1u], n);
+    }
+};
+
+// The node at i (kept: the node `slot`, behind a STORE of the value c),
+// compiled if it is not yet; kNone when the instruction at i has to be
+// stepped in general.
+template <int ISA>
+__device__ __forceinline__ uint32_t trace_compile(TraceTab &tr, int32_t i, const Regs &r, int32_t imax, uint32_t slot,
+                                                  int32_t c)
+{
+    const uint32_t n = r.n;
+    for (uint32_t tries = 0; tries < 4u; ++tries) {
+        uint32_t f = slot != kNone ? slot : tr.find(i);
+        if (f != kNone && tr.transitions(f) != 0) return f;
+        if (f == kNone && tr.nn >= tr.NO) { tr.drop_nodes(); ++tr.full; }
+        const bool kept = slot != kNone;
+        uint32_t k = 0, A = kNone, S = kNone, keep = kept ? 0u : 1u, op3 = 0;
+        bool known = kept, branch = false, trap = false, guard = false;
+        int32_t imm = kept ? c : 0, ii = i, target = 0;
+        uint64_t words = 0;
+        while (k < kTraceMax && ii <= imax - 4) {
+            const uint32_t p = cmod(ii, n), q = p + 1u == n ? 0u : p + 1u;
+            const uint32_t op = static_cast<uint32_t>(tr.M[p]);
+            const int32_t j = tr.M[q];
+            // an opcode that may have been stored to is not compiled; an
+            // operand that may have been is data to LOAD and PRINT
+            if (p == S || tr.stored(p)) break;
+            const bool dyn = q == S || tr.stored(q);
+            const uint32_t jj = cmod(j, n);
+            int32_t ni = ii + 2;
+            if (op == 1u) {
+                if (S != kNone) break;
+                keep = 0; op3 = 0;
+                known = !dyn;
+                imm = dyn ? 0 : j;
+                A = dyn ? q : kNone;
+            } else if (op == 7u) {
+                if (r.y0 < r.s) break;
+            } else if (dyn) {
+                break;
+            } else if (op == 2u || op == 3u) {
+                if (A != kNone || S != kNone) break;
+                A = jj;
+                op3 = op == 3u ? 1u : 0u;
+                known = false;
+            } else if (op == 4u) {
+                if (S != kNone) break;
+                if (!tr.stored(jj) && (((tr.code | words) & TraceTab::bit(jj)) != 0 || jj == p || jj == q)) {
+                    // nodes may rest on this word, now w
+                    const int32_t w = tr.M[jj];
+                    if (!(known && w == imm)) {
+                        if (k > 0 || kept) break;
+                        // the test a - w = 0, and what comes behind it
+                        guard = true;
+                        imm = static_cast<int32_t>(0u - static_cast<uint32_t>(w));
+                    }
+                    words |= TraceTab::bit(jj);          // holds as long as the word does
+                } else {
+                    S = jj;
+                }
+            } else if (op == 5u) {
+                if (known) {
+                    if (ISA == 1 ? imm > 0 : imm != 0) ni = j;
+                    if (ni == ii) break;
+                } else {
+                    branch = true;
+                    target = j;
+                    trap = j == ii;
+                }
+            } else if (ISA == 1 && op == 8u) {
+                if (j == ii) break;
+                ni = j;
+            } else {
+                break;
+            }
+            words |= TraceTab::bit(p) | TraceTab::bit(q);
+            ii = ni;
+            ++k;
+            if (branch | guard) break;
+        }
+        if (k == 0) return kNone;
+        // the data words and the successors' nodes; a full table is emptied
+        // (the node behind a kept word goes with the nodes: start at i)
+        const uint32_t fill = (A != kNone && tr.dfind(A) == kNone ? 1u : 0u) +
+                              (S != kNone && S != A && tr.dfind(S) == kNone ? 1u : 0u);
+        const bool own_f = !guard && !kept && ii == i, own_t = branch && !trap && !kept && target == i;
+        uint32_t xf = guard ? kNone : own_f ? f : tr.find(ii);
+        uint32_t xt = branch && !trap && !own_t ? tr.find(target) : kNone;
+        const bool one = !guard && (!branch || (!trap && target == ii));
+        const uint32_t more = (f == kNone ? 1u : 0u) + (xf == kNone && !own_f ? 1u : 0u) +
+                              (!one && !own_t && xt == kNone ? 1u : 0u);
+        if (tr.dn + fill > tr.ND || tr.nn + more > tr.NO) {
+            if (tr.dn + fill > tr.ND) tr.write_back();
+            tr.drop_nodes();
+            ++tr.full;
+            if (kept) return kNone;
+            continue;
+        }
+        if (f == kNone) f = tr.stub(i, kStub);
+        if (own_f) xf = f;
+        else if (xf == kNone) xf = tr.stub(ii, guard ? kKept : kStub);
+        if (guard) xt = tr.stub(i, kMiss);
+        else if (one) xt = xf;
+        else if (trap) xt = tr.stub(target, kTrap);
+        else if (own_t) xt = f;
+        else if (xt == kNone) xt = tr.stub(target, kStub);
+        uint32_t dA = tr.ND, dS = tr.ND + 1u;
+        if (A != kNone) {
+            dA = tr.dfind(A);
+            if (dA == kNone) dA = tr.add(A);
+        }
+        if (S != kNone) {
+            dS = tr.dfind(S);
+            if (dS == kNone) dS = tr.add(S);
+            tr.soil(dS, S);
+        }
+        li32 *const rec = &lds_i32(tr.node(f));
+        rec[0] = ISA == 1 ? static_cast<int32_t>(static_cast<uint32_t>(imm) + op3) : imm;
+        rec[1] = static_cast<int32_t>((tr.data(dA) << 14) | k);
+        rec[2] = static_cast<int32_t>((tr.data(dS) << 14) | (guard ? 1u << 13 : 0u) | (kept ? kKept << 11 | 4u : 0u) |
+                                      (f << 3) | (op3 << 1) | keep);
+        rec[3] = static_cast<int32_t>((static_cast<uint32_t>(i) & 0xffff0000u) | ((tr.node(xt) >> 10) << 8) |
+                                      (tr.node(xf) >> 10));
+        tr.code |= words;
+        return f;
+    }
+    return kNone;
+}
+
+// One transition in general, memory in the lane's data words and HBM.
+// Returns false, changing nothing, when the machine is at a fixed point or
+// has no transition left.
+template <int ISA, bool WM>
+__device__ __forceinline__ bool trace_step(TraceTab &tr, Regs &r, const gi32 *T, gi32 *Y, uint32_t left, bool &halted,
+                                           uint32_t ws, int32_t imax)
+{
+    const uint32_t n = r.n;
+    const uint32_t p = cmod(r.i, n), q = operand_pos(r.i, p, n, imax);
+    const uint32_t op = static_cast<uint32_t>(tr.ld(p));
+    const int32_t j = tr.ld(q);
+    halted = stuck<ISA>(op, j, r.a, r.i, r.u0, r.ell);
+    if (halted || left == 0) return false;
+    const bool taken = ISA == 1 ? (op == 8u) | ((op == 5u) & (r.a > 0)) : (op == 5u) & (r.a != 0);
+    const bool app = (op == 7u) & (r.y0 < r.s);
+    const uint32_t jj = cmod(j, n);
+    int32_t d = 0;
+    if ((op == 2u) | (op == 3u) | app) d = tr.ld(jj);
+    if ((op == 4u) | (op == 6u)) {
+        int32_t w = r.a;
+        if (op == 6u) w = T[r.u0++];
+        tr.st(jj, w);
+    }
+    if (app) Y[r.y0++] = d;
+    r.a = accumulate<ISA, WM>(op, r.a, d, j, ws);
+    const uint32_t i2 = static_cast<uint32_t>(r.i) + 2u;
+    r.i = taken ? j : (WM ? sext(i2, ws) : static_cast<int32_t>(i2));
+    return true;
+}
+
+template <int ISA, bool WM>
+__global__ __launch_bounds__(kWave) void k_trace(const BatchTable *__restrict__ tab, uint32_t already, TraceArgs ta,
+                                                 QueueState *__restrict__ q)
+{
+    const uint32_t lane = threadIdx.x;
+    const uint64_t total = ta.in == kListFirst ? q->survivors : q->count[ta.in];
+    unsigned long long *const head = ta.in == kListFirst ? &q->head : &q->next[ta.in];
+    // few machines are spread over the launch's waves: a wave waits for
+    // every lane that compiles or steps in general
+    const uint64_t share = (total + gridDim.x - 1u) / gridDim.x;
+    const uint32_t lanes = static_cast<uint32_t>(share < 64u ? (share < 1u ? 1u : share) : 64u);
+    TraceTab tr;
+    tr.NO = ta.NO;
+    tr.ND = ta.ND;
+    tr.nb = 16u * lane;
+    tr.db = (ta.NO << 10) + 4u * lane;
+    tr.kb = (ta.NO << 10) + ((ta.ND + 2u) << 8) + 2u * lane;
+    tr.pb = tr.kb + (ta.NO << 7);
+    tr.nn = tr.dn = tr.ev = tr.full = 0;
+    tr.code = tr.keys = tr.held = tr.dirty = 0;
+    tr.M = nullptr;
+    lds_i32(tr.data(ta.ND)) = 0;
+
+    bool has = false, exhausted = false;
+    Regs r{};
+    gi32 *T = nullptr, *Y = nullptr;
+    const DevBatch *bp = nullptr;
+    uint64_t v = 0;
+    uint32_t gid = 0, left = 0, limit = 0, reads = 0, ws = 0, cur = kNone, span = 8u;
+    int32_t imax = INT32_MAX;
+
+    for (;;) {
+        // ---- refill: when a quarter of the lanes idle ----
+        const uint64_t idle = __ballot(!has && lane < lanes);
+        const uint32_t nidle = __popcll(idle);
+        if (!exhausted && 4u * nidle >= lanes) {
+            const int leader = __ffsll(static_cast<unsigned long long>(idle)) - 1;
+            unsigned long long base = 0;
+            if (lane == static_cast<uint32_t>(leader))
+                base = __hip_atomic_fetch_add(head, static_cast<unsigned long long>(nidle), __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+            base = __shfl(base, leader);
+            if (base + nidle >= total) exhausted = true;
+            if (!has && lane < lanes) {
+                const uint64_t item = base + __popcll(idle & ((1ull << lane) - 1ull));
+                if (item < total) {
+                    gid = ta.idx[ta.in][item];
+                    const int k = batch_of(tab, gid);
+                    bp = &tab->b[k];
+                    v = gid - tab->start[k];
+                    const uint32_t budget = tab->budget[k];
+                    if (gany(bp->status)[v] == 0 && budget > already) {
+                        r.n = gany(bp->n)[v]; r.ell = gany(bp->ell)[v]; r.s = gany(bp->s)[v];
+                        r.i = gany(bp->i)[v]; r.a = gany(bp->a)[v];
+                        r.u0 = gany(bp->u0)[v]; r.y0 = gany(bp->y0)[v];
+                        ws = bp->wshift;
+                        imax = WM ? static_cast<int32_t>(0x7fffffffu >> ws) : INT32_MAX;
+                        tr.M = gptr(bp->M + gany(bp->mem_off)[v]);
+                        T = gptr(bp->T + gany(bp->t_off)[v]);
+                        Y = gptr(bp->Y + gany(bp->y_off)[v]);
+                        tr.nn = tr.dn = tr.ev = tr.full = 0;
+                        tr.code = tr.keys = tr.held = tr.dirty = 0;
+                        left = limit = ta.left[ta.in] ? ta.left[ta.in][item] : budget - already;
+                        reads = 0;
+                        cur = kNone;
+                        has = true;
+                    }
+                }
+            }
+            span = 8u;
+        }
+        if (__ballot(has) == 0) {
+            if (exhausted) break;
+            continue;
+        }
+        // ---- bring every lane to a compiled node, or out of here ----
+        bool ready = false, halted = false, step = false;
+        uint32_t to = kNone;                                   // the list a machine leaves for (kListDone: none)
+        for (uint32_t round = 0; round < kTraceRounds; ++round) {
+            const bool want = has && !ready && to == kNone;
+            if (__ballot(want) == 0) break;
+            if (want) {
+                uint32_t slot = kNone;
+                int32_t c = 0;
+                if (left < kTraceMax * kTraceEnd) to = kListEnd;
+                if (cur != kNone) {
+                    const uint32_t x = (cur - tr.nb) >> 10;
+                    const uint32_t kd = tr.kind(x);
+                    ready = tr.transitions(x) != 0 && to == kNone;
+                    if (!ready) {                              // leave the node
+                        r.i = tr.at(x);
+                        if (kd == kTrap) {
+                            // the jump onto itself was counted: no
+                            // transition but a fixed point
+                            ++left;
+                            halted = true;
+                            to = kListDone;
+                        } else if (kd == kMiss) {
+                            // undo the test, step the STORE in general
+                            const uint32_t w = static_cast<uint32_t>(tr.M[tr.target(r.i, r.n)]) + static_cast<uint32_t>(r.a);
+                            r.a = WM ? sext(w, ws) : static_cast<int32_t>(w);
+                            ++left;
+                            step = true;
+                        } else if (kd == kKept) {
+                            r.a = c = tr.M[tr.target(r.i - 2, r.n)];
+                            slot = x;
+                        }
+                        cur = kNone;
+                    }
+                }
+                if (!ready && to == kNone) {
+                    uint32_t x = kNone;
+                    if (!step) x = trace_compile<ISA>(tr, r.i, r, imax, slot, c);
+                    step = false;
+                    const uint32_t done = limit - left;
+                    const bool often = tr.ev > kTraceEvents + (done >> 11);
+                    if (often || tr.full > kTraceFulls + (done >> 10)) {
+                        // (a kept word's value is in r.a already; a machine
+                        // whose i has left its memory never comes back to
+                        // the same i)
+                        if (often || static_cast<uint32_t>(r.i) >= r.n) to = ta.in == kListFull ? kListLast : kListGeneral;
+                        else to = ta.in == kListFull ? kListLast : kListFull;
+                    } else if (x != kNone) {
+                        cur = tr.node(x);
+                        ready = true;
+                    } else if (const uint32_t u = r.u0; trace_step<ISA, WM>(tr, r, T, Y, left, halted, ws, imax)) {
+                        // (a loop that reads a short tape ends with it soon)
+                        reads += r.u0 - u;
+                        if (r.u0 == u || reads > kTapeLdsMax) ++tr.ev;
+                        --left;
+                    } else {
+                        to = kListDone;
+                    }
+                }
+            }
+        }
+        // ---- run macro steps: until few transitions are left to some lane,
+        // which then waits for others to come as far ----
+        const bool near = ready && left < kTraceMax * kTraceNear;
+        const uint64_t far_m = __ballot(ready && !near), near_m = __ballot(near);
+        const bool tail = far_m == 0 || 4u * static_cast<uint32_t>(__popcll(near_m)) >= lanes;
+        const bool go = ready && (tail || !near);
+        if ((far_m | near_m) != 0) {
+            const bool wait = __ballot(has && !ready && to == kNone) != 0;
+            uint32_t steps = wave_min(go ? left / kTraceMax : ~0u);
+            if (steps > span) steps = span;
+            if (wait && steps > 8u) steps = 8u;
+            bool stubbed = false;
+            if (go) {
+                uint32_t acc = 0;
+                int32_t a = r.a;
+                v4i w = *reinterpret_cast<const lv4i *>(cur);
+#pragma unroll 4
+                for (uint32_t t = steps; t != 0; --t) {
+                    const uint32_t y = static_cast<uint32_t>(w[1]), z = static_cast<uint32_t>(w[2]);
+                    const uint32_t nx = static_cast<uint32_t>(w[3]);
+                    // both successors' records beside the data word: the next
+                    // step waits for one LDS round trip, not two (137 against
+                    // 167 cycles a step for one wave, 16.5 against 17.7 a
+                    // step and CU with ten)
+                    const int32_t d = lds_i32(y >> 14);
+                    const v4i wf = *reinterpret_cast<const lv4i *>(((nx & 0xffu) << 10) | (16u * lane));
+                    const v4i wt = *reinterpret_cast<const lv4i *>((__builtin_amdgcn_ubfe(nx, 8u, 8u) << 10) | (16u * lane));
+                    acc += y << 16;
+                    const int32_t keep = static_cast<int32_t>(z << 31) >> 31, m = static_cast<int32_t>(z << 30) >> 31;
+                    const uint32_t b = static_cast<uint32_t>(a & keep) + static_cast<uint32_t>(w[0]);
+                    uint32_t x;
+                    if (ISA == 1) {
+                        x = static_cast<uint32_t>(d ^ m) + b;
+                    } else {
+                        const uint32_t sum = b + static_cast<uint32_t>(d), mul = b * static_cast<uint32_t>(d);
+                        x = (mul & static_cast<uint32_t>(m)) | (sum & ~static_cast<uint32_t>(m));
+                    }
+                    a = WM ? sext(x, ws) : static_cast<int32_t>(x);
+                    lds_i32(z >> 14) = a;
+                    // a > 0 as a - 1 < 2^31 - 1, or a != 0 as a - 1 < 2^32 - 1
+                    const bool tk = ISA == 1 ? static_cast<uint32_t>(a) - 1u < ((z << 18) | 0x7fffffffu) : a != 0;
+                    w[0] = tk ? wt[0] : wf[0];
+                    w[1] = tk ? wt[1] : wf[1];
+                    w[2] = tk ? wt[2] : wf[2];
+                    w[3] = tk ? wt[3] : wf[3];
+                }
+                r.a = a;
+                left -= acc >> 16;
+                cur = tr.node((static_cast<uint32_t>(w[2]) >> 3) & 0xffu);
+                stubbed = (w[1] & 0xffff) == 0;
+            }
+            // stubs are looked for seldom once they are rare
+            span = __ballot(stubbed) != 0 ? (span > 16u ? span >> 2 : 4u) : (span < 1024u ? span << 1 : span);
+        }
+        // ---- machines that leave: memory and state to HBM ----
+        if (to != kNone) {
+            tr.write_back();
+            if (left != limit) {
+                gany(bp->i)[v] = r.i; gany(bp->a)[v] = r.a; gany(bp->u0)[v] = r.u0; gany(bp->y0)[v] = r.y0;
+                gany(bp->steps)[v] += limit - left;
+            }
+            if (halted) gany(bp->status)[v] = 1;
+            has = false;
+        }
+        if (__ballot(to != kNone) != 0)
+            for (uint32_t l = kListGeneral; l <= kListEnd; ++l) {
+                if (__ballot(to == l) == 0) continue;
+                const uint64_t e = wave_append(to == l, &q->count[l], lane);
+                if (to == l) {
+                    ta.idx[l][e] = gid;
+                    ta.left[l][e] = left;
+                }
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// K3 with whole memories in LDS, 2^sh lanes a wave: the machines that do not
+// run in nodes.  Word k of lane l's memory is LDS word (k << sh) + l; word n
+// takes the stores that do not happen.  The lanes step in lockstep, so a wave
+// of few lanes takes a transition as fast as a full one, and memories of up
+// to 1,024 words fit.  A list of more than ta.few machines is left to the
+// work queue.
+// A transition's bound is its chain at one wave a SIMD: some 35 vector
+// instructions and one LDS round trip.  The loop has one exit, at its end,
+// where the next instruction is known: it goes on while that is common for
+// every lane (as in run_lockstep: no READ, append, HALT, jump onto itself or
+// counter near the largest word) and transitions are left.
+// ---------------------------------------------------------------------------
+template <int ISA, bool POW2, bool WM, uint32_t SH>
+__device__ __forceinline__ uint32_t run_whole(uint32_t base, const gi32 *T, gi32 *Y, Regs &r, uint32_t L, bool &halted,
+                                              uint32_t ws)
+{
+    constexpr uint32_t kCommon = ISA == 1 ? 0x1beu : 0xbeu;
+    constexpr uint32_t kWord = 4u << SH;                 // bytes between a memory's words
+    const uint32_t n = r.n, nm = n - 1u, spare = base + n * kWord;
+    const int32_t imax = WM ? static_cast<int32_t>(0x7fffffffu >> ws) : INT32_MAX;
+    uint32_t rinv = 0, big = 0;          // as in run_lockstep
+    if (!POW2 && n >= 2u) {
+        rinv = 0xffffffffu / n;
+        big = (0x80000000u / n + (0x80000000u % n != 0u)) * n;
+    }
+    uint32_t p = r.p, u0 = r.u0, y0 = r.y0;
+    int32_t i = r.i, a = r.a;
+    auto ld = [&](uint32_t k) { return static_cast<int32_t>(lds_i32(base + k * kWord)); };
+    int32_t o = ld(p), j = ld(POW2 ? ((p + 1u) & nm) : operand_pos(i, p, n, imax));
+    uint32_t left = L;
+    // ~0 if opcode k has its bit in set (k capped at 31): choices are masks in
+    // vector registers, since a lane mask passed to the scalar unit and back
+    // waits for both
+    auto in = [](uint32_t set, uint32_t k) {
+        return static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(set), k, 1u));
+    };
+    auto pick = [](uint32_t mask, uint32_t x, uint32_t y) { return (mask & x) | (~mask & y); };
+    const int32_t top = imax - 5;
+    for (;;) {
+        const uint32_t cold = n < 2u ? ~0u : (~kCommon | (y0 < r.s ? 0x80u : 0u));
+        // what the instruction at hand does next: the next value of i and its
+        // position, and the LDS word of the data (of the next instruction if
+        // there is none); returns 0 for a lane it is not common for
+        uint32_t ni = 0, np = 0, ad = 0, k = 0;
+        auto decode = [&]() -> uint32_t {
+            k = min(static_cast<uint32_t>(o), 31u);
+            const uint32_t ua = static_cast<uint32_t>(a), uj = static_cast<uint32_t>(j);
+            // the sign of -a & ~a: a > 0
+            const uint32_t test = ISA == 1 ? static_cast<uint32_t>(static_cast<int32_t>((0u - ua) & ~ua) >> 31)
+                                           : (a != 0 ? ~0u : 0u);
+            const uint32_t tk = (in(0x20u, k) & test) | (ISA == 1 ? in(0x100u, k) : 0u), us = in(0x1cu, k);
+            const uint32_t i2 = static_cast<uint32_t>(i) + 2u;
+            ni = pick(tk, uj, WM ? static_cast<uint32_t>(sext(i2, ws)) : i2);
+            uint32_t jm = uj;
+            const uint32_t q = p + 2u;
+            if (POW2) {
+                jm &= nm;
+                np = pick(tk, jm, q & nm);
+            } else {
+                if (__builtin_expect(any_lane((uj & (us | tk)) >= n), 0)) {
+                    const uint32_t u = uj + (j < 0 ? big : 0u);
+                    const uint32_t rr = u - __umulhi(u, rinv) * n;
+                    jm = min(rr, rr - n);
+                }
+                np = pick(tk, jm, min(q, q - n));
+            }
+            ad = base + pick(us, jm, np) * kWord;
+            // jumps onto themselves, uncommon opcodes, an operand that wraps
+            // to word 0, a counter near the largest word
+            uint32_t ok = min((ni ^ static_cast<uint32_t>(i)) & ~in(cold, k), np ^ nm);
+            if (!POW2 || WM)
+                ok = min(ok, static_cast<uint32_t>(min(static_cast<int32_t>(ni), top)) ^ static_cast<uint32_t>(top));
+            return ok;
+        };
+        uint32_t ok = decode();
+        if (!any_lane(min(ok, left) == 0u)) {
+            do {
+                const uint32_t nx = base + np * kWord;
+                lds_i32(pick(in(0x10u, k), ad, spare)) = a;
+                const int32_t o2 = lds_i32(nx), j2 = lds_i32(nx + kWord);
+                const uint32_t d = static_cast<uint32_t>(static_cast<int32_t>(lds_i32(ad)));
+                const uint32_t ua = static_cast<uint32_t>(a), m3 = in(0x8u, k);
+                uint32_t x;
+                if (ISA == 1) x = ua + (((d ^ m3) - m3) & in(0xcu, k));
+                else x = pick(m3, ua * d, ua + (d & in(0x4u, k)));
+                if (WM) x = static_cast<uint32_t>(sext(x, ws));
+                a = static_cast<int32_t>(pick(in(0x2u, k), static_cast<uint32_t>(j), x));
+                i = static_cast<int32_t>(ni);
+                p = np;
+                o = o2;
+                j = j2;
+                --left;
+                ok = min(decode(), left);
+            } while (!any_lane(ok == 0u));
+        }
+        if (left == 0) break;
+        // a transition that is not common for some lane, with general positions
+        if (any_lane(stuck<ISA>(static_cast<uint32_t>(o), j, a, i, u0, r.ell))) break;
+        const bool taken = ISA == 1 ? (o == 8) | ((o == 5) & (a > 0)) : (o == 5) & (a != 0);
+        const bool rd = o == 6, app = (o == 7) & (y0 < r.s);
+        const uint32_t jj = cmod(j, n);
+        np = taken ? jj : advance_pos(i, p, n, imax, WM ? ws : 0u);
+        const uint32_t nq = operand_pos(static_cast<int32_t>(ni), np, n, imax);
+        int32_t w = a;
+        if (rd) w = T[u0++];
+        if (rd | (o == 4)) lds_i32(base + jj * kWord) = w;
+        const int32_t d = ld(jj);
+        if (app) Y[y0++] = d;
+        a = accumulate<ISA, WM>(static_cast<uint32_t>(o), a, d, j, ws);
+        o = ld(np);
+        j = ld(nq);
+        i = static_cast<int32_t>(ni);
+        p = np;
+        --left;
+    }
+    halted = stuck<ISA>(static_cast<uint32_t>(o), j, a, i, u0, r.ell);
+    r.i = i; r.a = a; r.p = p; r.u0 = u0; r.y0 = y0;
+    return L - left;
+}
+
+template <int ISA, bool POW2, uint32_t SH>
+__global__ __launch_bounds__(kWave) void k_whole(const BatchTable *__restrict__ tab, TraceArgs ta, uint32_t wm,
+                                                 QueueState *__restrict__ q)
+{
+    const uint32_t lane = threadIdx.x;
+    const uint64_t total = q->count[ta.in];
+    if (total > ta.few) return;
+    // as many a wave as spreads them over the launch, at most 2^SH
+    const uint64_t even = (total + gridDim.x - 1u) / gridDim.x;
+    const uint32_t share = static_cast<uint32_t>(even < (1u << SH) ? (even < 1u ? 1u : even) : (1u << SH));
+    for (;;) {
+        unsigned long long first = 0;
+        if (lane == 0)
+            first = __hip_atomic_fetch_add(&q->next[ta.in], static_cast<unsigned long long>(share), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+        first = __shfl(first, 0);
+        if (first >= total) break;
+        const uint64_t item = first + lane;
+        bool has = lane < share && item < total;
+        Regs r{};
+        gi32 *M = nullptr, *T = nullptr, *Y = nullptr;
+        const DevBatch *bp = nullptr;
+        uint64_t v = 0;
+        uint32_t left = 0, limit = 0, ws = 0;
+        if (has) {
+            const uint32_t gid = ta.idx[ta.in][item];
+            const int k = batch_of(tab, gid);
+            bp = &tab->b[k];
+            v = gid - tab->start[k];
+            r.n = gany(bp->n)[v]; r.ell = gany(bp->ell)[v]; r.s = gany(bp->s)[v];
+            r.i = gany(bp->i)[v]; r.a = gany(bp->a)[v];
+            r.u0 = gany(bp->u0)[v]; r.y0 = gany(bp->y0)[v];
+            r.p = cmod(r.i, r.n);
+            ws = bp->wshift;
+            M = gptr(bp->M + gany(bp->mem_off)[v]);
+            T = gptr(bp->T + gany(bp->t_off)[v]);
+            Y = gptr(bp->Y + gany(bp->y_off)[v]);
+            left = limit = ta.left[ta.in][item];
+        }
+        const uint32_t top = wave_max(has ? r.n : 0u);
+        for (uint32_t k = 0; k < top; ++k)
+            if (has && k < r.n) dma4((const int32_t *)(M + k), k << SH);
+        __builtin_amdgcn_s_waitcnt(0);
+        while (__ballot(has) != 0) {
+            const uint32_t L = wave_min(has ? left : ~0u);
+            if (has) {
+                bool halted;
+                left -= wm ? run_whole<ISA, POW2, true, SH>(4u * lane, T, Y, r, L, halted, ws)
+                           : run_whole<ISA, POW2, false, SH>(4u * lane, T, Y, r, L, halted, 0u);
+                if (halted || left == 0) {
+                    for (uint32_t k = 0; k < r.n; ++k) M[k] = lds_i32(4u * lane + (k << (SH + 2u)));
+                    gany(bp->i)[v] = r.i; gany(bp->a)[v] = r.a; gany(bp->u0)[v] = r.u0; gany(bp->y0)[v] = r.y0;
+                    gany(bp->steps)[v] += limit - left;
+                    if (halted) gany(bp->status)[v] = 1;
+                    has = false;
+                }
+            }
+        }
+    }
+}
+
+template <int ISA, bool POW2>
+static void whole_go(unsigned blocks, size_t shmem, hipStream_t st, const BatchTable *tab, const TraceArgs &ta, uint32_t sh,
+                     uint32_t wm, QueueState *q)
+{
+    if (sh == 6u) k_whole<ISA, POW2, 6><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
+    else if (sh == 5u) k_whole<ISA, POW2, 5><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
+    else if (sh == 4u) k_whole<ISA, POW2, 4><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
+    else k_whole<ISA, POW2, 3><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
+}
+
+hipError_t launch_whole(const BatchTable *tab, uint32_t isa, bool pow2, bool wmb, const TraceArgs &ta, uint32_t sh,
+                        uint32_t max_n, uint32_t blocks, QueueState *q, hipStream_t st)
+{
+    const size_t shmem = whole_lds_bytes(max_n, sh);
+    const uint32_t wm = wmb ? 1u : 0u;
+    if (sh < 3u || sh > 6u) return hipErrorInvalidValue;
+    if (isa == 1) {
+        if (pow2) whole_go<1, true>(blocks, shmem, st, tab, ta, sh, wm, q);
+        else whole_go<1, false>(blocks, shmem, st, tab, ta, sh, wm, q);
+    } else {
+        if (pow2) whole_go<0, true>(blocks, shmem, st, tab, ta, sh, wm, q);
+        else whole_go<0, false>(blocks, shmem, st, tab, ta, sh, wm, q);
+    }
+    return hipGetLastError();
+}
+
+template <int ISA, bool POW2, uint32_t SH>
+static void whole_attr()
+{
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_whole<ISA, POW2, SH>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+}
+
+hipError_t launch_trace(const BatchTable *tab, uint32_t already, uint32_t isa, bool wm, const TraceArgs &ta,
+                        uint32_t blocks, QueueState *q, hipStream_t st)
+{
+    const dim3 grid(blocks), block(kWave);
+    const size_t shmem = trace_lds_bytes(ta.NO, ta.ND);
+    if (isa == 1) {
+        if (wm) k_trace<1, true><<<grid, block, shmem, st>>>(tab, already, ta, q);
+        else k_trace<1, false><<<grid, block, shmem, st>>>(tab, already, ta, q);
+    } else {
+        if (wm) k_trace<0, true><<<grid, block, shmem, st>>>(tab, already, ta, q);
+        else k_trace<0, false><<<grid, block, shmem, st>>>(tab, already, ta, q);
+    }
+    return hipGetLastError();
+}
+
 template <int ISA, int MODE, bool POW2, bool TLDS>
 static hipError_t launch_k3(dim3 grid, dim3 block, size_t shmem, hipStream_t st, const BatchTable *tab,
                             uint64_t total, const uint32_t *work, uint32_t already, uint32_t epoch,
                             uint32_t P, uint32_t TL, uint32_t wm, uint32_t cap, uint32_t *surv, QueueState *q,
-                            uint32_t which)
+                            uint32_t which, const uint32_t *rest_left, uint32_t few)
 {
     k_persistent<ISA, MODE, POW2, TLDS><<<grid, block, shmem, st>>>(tab, total, work, already, epoch, P, TL,
-                                                                    wm, cap, surv, q, which);
+                                                                    wm, cap, surv, q, which, rest_left, few);
     return hipGetLastError();
 }
 
@@ -1785,6 +2598,13 @@ void init_kernel_attributes()
                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_persistent_hot<1, true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    for (const void *k : {reinterpret_cast<const void *>(&k_trace<0, false>), reinterpret_cast<const void *>(&k_trace<0, true>),
+                          reinterpret_cast<const void *>(&k_trace<1, false>), reinterpret_cast<const void *>(&k_trace<1, true>)})
+        (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    whole_attr<0, false, 3>(); whole_attr<0, false, 4>(); whole_attr<0, false, 5>(); whole_attr<0, false, 6>();
+    whole_attr<0, true, 3>(); whole_attr<0, true, 4>(); whole_attr<0, true, 5>(); whole_attr<0, true, 6>();
+    whole_attr<1, false, 3>(); whole_attr<1, false, 4>(); whole_attr<1, false, 5>(); whole_attr<1, false, 6>();
+    whole_attr<1, true, 3>(); whole_attr<1, true, 4>(); whole_attr<1, true, 5>(); whole_attr<1, true, 6>();
     (void)hipGetLastError();
 }
 
@@ -1792,10 +2612,11 @@ template <int ISA, int MODE, bool TLDS>
 static hipError_t launch_k3_p(bool pow2, dim3 grid, dim3 block, size_t shmem, hipStream_t st,
                               const BatchTable *tab, uint64_t total, const uint32_t *work,
                               uint32_t already, uint32_t epoch, uint32_t P, uint32_t TL,
-                              uint32_t wm, uint32_t cap, uint32_t *surv, QueueState *q, uint32_t which)
+                              uint32_t wm, uint32_t cap, uint32_t *surv, QueueState *q, uint32_t which,
+                              const uint32_t *rest_left, uint32_t few)
 {
-    return pow2 ? launch_k3<ISA, MODE, true, TLDS>(grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which)
-                : launch_k3<ISA, MODE, false, TLDS>(grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which);
+    return pow2 ? launch_k3<ISA, MODE, true, TLDS>(grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few)
+                : launch_k3<ISA, MODE, false, TLDS>(grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few);
 }
 
 // the tape is staged in LDS when every memory fits its slot and every tape
@@ -1812,10 +2633,9 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
                              uint32_t already, uint32_t isa, bool pow2, bool wmb, uint32_t epoch,
                              uint32_t lds_words, uint32_t max_n, uint32_t max_ell,
                              uint32_t waves_per_block, uint32_t blocks, uint32_t cap, uint32_t *surv,
-                             QueueState *q, hipStream_t st, bool misfits)
+                             QueueState *q, hipStream_t st, uint32_t which, const uint32_t *rest_left, uint32_t few)
 {
     const uint32_t wm = wmb ? 1u : 0u;
-    const uint32_t which = misfits ? 1u : 0u;
     const dim3 grid(blocks), block(waves_per_block * kWave);
     const int mode = lds_words == 0 ? 0 : (max_n <= lds_words ? 1 : 2);
     const uint32_t P = mode == 0 ? 0u : lds_words;
@@ -1823,15 +2643,15 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
     const uint32_t TL = (mode == 1 && SPw > P + 4u) ? SPw - P - 4u : 0u;
     const size_t shmem = mode == 0 ? 0 : static_cast<size_t>(waves_per_block) * kWave * SPw * sizeof(int32_t);
     if (isa == 1) {
-        if (mode == 1 && TL) return launch_k3_p<1, 1, true>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which);
-        if (mode == 1) return launch_k3_p<1, 1, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which);
-        if (mode == 2) return launch_k3_p<1, 2, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which);
-        return launch_k3_p<1, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which);
+        if (mode == 1 && TL) return launch_k3_p<1, 1, true>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few);
+        if (mode == 1) return launch_k3_p<1, 1, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
+        if (mode == 2) return launch_k3_p<1, 2, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
+        return launch_k3_p<1, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
     }
-    if (mode == 1 && TL) return launch_k3_p<0, 1, true>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which);
-    if (mode == 1) return launch_k3_p<0, 1, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which);
-    if (mode == 2) return launch_k3_p<0, 2, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which);
-    return launch_k3_p<0, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which);
+    if (mode == 1 && TL) return launch_k3_p<0, 1, true>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few);
+    if (mode == 1) return launch_k3_p<0, 1, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
+    if (mode == 2) return launch_k3_p<0, 2, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
+    return launch_k3_p<0, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
 }
 
 __global__ void k_zero_queue(QueueState *q, uint32_t head_only)
@@ -1839,7 +2659,8 @@ __global__ void k_zero_queue(QueueState *q, uint32_t head_only)
     if (threadIdx.x == 0) {
         q->head = 0;
         q->head_m = 0;
-        if (!head_only) { q->survivors = 0; q->retired = 0; q->pad = 0; q->misfits = 0; }
+        for (int k = 0; k < kLists; ++k) q->next[k] = 0;
+        if (!head_only) { q->survivors = 0; q->retired = 0; q->pad = 0; q->misfits = 0; for (int k = 0; k < kLists; ++k) q->count[k] = 0; }
     }
 }
 

@@ -23,6 +23,17 @@ constexpr uint64_t kAlign = 256;
 constexpr int kTableRing = 16;
 constexpr int kTickets = 4;              // running-count requests in flight per context
 static_assert(sizeof(BatchTable) >= 8 * kMaxMulti * kTickets, "device count slots fit one table slot");
+// fewest transitions left after the first pass for which the survivors are
+// compiled into traces: some 40 us of launches and a few compilations a machine
+// (about 5 us each, in turn with the wave's other lanes) against 0.3 us
+// (memories whole in LDS) or 0.8-1.6 us (HBM) a transition in lockstep.
+// plain-scale with 4,096 left, whole in LDS: 1.9 ms with traces, 1.68 without;
+// 50,021 uneven machines with 16,320 left, in HBM: 5.7 ms against 6.8.
+constexpr uint32_t kTraceMinLeft = 2048, kTraceMinLeftLds = 8192;
+// transitions after which transients are over: traces start there
+constexpr uint32_t kTraceWarm = 512;
+constexpr uint32_t kWholeRounds = 2;      // times k_whole's lanes are filled at most
+constexpr uint64_t kLdsGrain = 1280;      // LDS of a block is taken in units of this
 constexpr uint64_t kStageWords = 32ull << 20;    // host-load staging: program + input words per chunk
 constexpr uint64_t kStageVms = 1ull << 20;       // and machines per chunk
 
@@ -183,6 +194,8 @@ struct rasp_ctx {
     int table_next = 0;
     Alloc work;                          // survivor list
     uint64_t work_cap = 0;
+    Alloc trace;                         // the trace kernel's lists
+    uint64_t trace_cap = 0;
     uint32_t *err_host = nullptr;        // pinned: error word and totals
     uint64_t *tot_host = nullptr;
     uint64_t *count_host = nullptr;      // pinned: running counts, kTickets x kMaxMulti
@@ -236,7 +249,14 @@ int fail(rasp_ctx *c, int code, const char *fmt, ...)
 
 bool arena_alloc(rasp_ctx *c, uint64_t bytes, Alloc *a)
 {
-    if (!c->alloc.alloc(bytes, &a->off)) return false;
+    if (!c->alloc.alloc(bytes, &a->off)) {
+        // the trace kernel's lists are only taken where there is room for them
+        if (!c->trace.live || a == &c->trace || hipStreamSynchronize(c->stream) != hipSuccess) return false;
+        c->alloc.release(c->trace.off, c->trace.bytes);
+        c->trace.live = false;
+        c->trace_cap = 0;
+        if (!c->alloc.alloc(bytes, &a->off)) return false;
+    }
     a->bytes = bytes;
     a->live = true;
     return true;
@@ -646,6 +666,21 @@ int ensure_work(rasp_ctx *c, uint64_t items)
     return RASP_OK;
 }
 
+// room for the trace kernel's lists of `items` machines; false: none, and the
+// run goes without traces
+bool ensure_trace(rasp_ctx *c, uint64_t items)
+{
+    if (items <= c->trace_cap) return true;
+    if (c->trace.live) {
+        if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
+        arena_free(c, &c->trace);
+    }
+    c->trace_cap = 0;
+    if (!arena_alloc(c, 9 * align_up(4 * items, kAlign), &c->trace)) return false;
+    c->trace_cap = items;
+    return true;
+}
+
 // ensure the hot-cell arrays hold `items` survivor-list entries of S slots
 int ensure_hot(rasp_ctx *c, uint64_t items, uint64_t S)
 {
@@ -892,12 +927,16 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
         HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] { return hipGraphLaunch(ex, st); }));
         return RASP_OK;
     }
+    // traces: survivors with a budget worth compiling for, in a launch that may allocate
+    const bool trace = sched == RASP_SCHED_PERSISTENT && cap > 0 && cap < maxb &&
+                       maxb - cap >= (P >= max_n ? kTraceMinLeftLds : kTraceMinLeft) &&
+                       max_n <= kTraceMaxN && rs == nullptr && ensure_work(c, total) == RASP_OK && ensure_trace(c, total);
     if (fused) {
         // fresh batches present: one persistent launch over every machine
         HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
             return launch_persistent(dt, total, nullptr, 0, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap, nullptr, qs, st); }));
         for (uint32_t t = 0; t < k; ++t) bs[t]->dev.fresh = 0;
-    } else if (hot) {
+    } else if (hot && !trace) {
         // hot-cell first pass (plain, profiling its last transitions), then
         // the persistent kernel over fits and misfits with their LDS tables
         if ((rc = ensure_work(c, total)) || (rc = ensure_hot(c, total, S_hot))) return rc;
@@ -936,7 +975,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
         HIPCHK(c, hipStreamWaitEvent(st2, c->ev_first, 0));
         HIPCHK(c, timed_launch(c, RASP_KERNEL_MISFIT, [&] {
             return launch_persistent(dt2, total, ha.mis, cap, isa, pow2, wm, epoch, 0u, max_n, max_ell, 4u, blocks_m,
-                                     kNoCap, nullptr, qs, st2, true); }, st2));
+                                     kNoCap, nullptr, qs, st2, 1u); }, st2));
         HIPCHK(c, hipEventRecord(c->ev_second, st2));
         HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
             return launch_persistent_hot(dt2, work, cap, isa, pow2, wm, epoch, ha, wpb_h, blocks_h, qs, st); }));
@@ -972,8 +1011,69 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             HIPCHK(c, hipEventRecord(c->table_ev[slot2], st));
             c->table_used[slot2] = true;
         }
-        HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
-            return launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap, nullptr, qs, st); }));
+        if (trace) {
+            TraceArgs ta{};
+            const uint64_t list = align_up(4 * c->trace_cap, kAlign);
+            uint64_t part = 0;
+            ta.idx[kListFirst] = work;
+            ta.idx[kListWarm] = at<uint32_t>(c, c->trace, part++ * list);
+            for (uint32_t l : {kListGeneral, kListFull, kListLast, kListEnd}) {
+                ta.idx[l] = at<uint32_t>(c, c->trace, part++ * list);
+                ta.left[l] = at<uint32_t>(c, c->trace, part++ * list);
+            }
+            // transients first: another pass, over the survivors
+            const bool warm = cap < kTraceWarm && maxb > kTraceWarm;
+            const uint32_t from = warm ? kListWarm : kListFirst, ran = warm ? kTraceWarm : cap;
+            auto traces = [&](uint32_t in, uint32_t NO, uint32_t ND) {
+                ta.in = in;
+                ta.NO = NO;
+                ta.ND = ND;
+                const uint64_t per_cu = lds / align_up(trace_lds_bytes(NO, ND), kLdsGrain);
+                const uint64_t waves_t = std::min<uint64_t>(total, per_cu * static_cast<uint64_t>(c->cus));
+                return launch_trace(dt2, ran, isa, wm, ta, static_cast<uint32_t>(waves_t), qs, st);
+            };
+            auto queue = [&](uint32_t in, uint32_t Pw, uint32_t wpbw, uint32_t blocksw, uint32_t few, hipStream_t on) {
+                return launch_persistent(dt2, total, ta.idx[in], ran, isa, pow2, wm, epoch, Pw, max_n, max_ell, wpbw, blocksw,
+                                         kNoCap, nullptr, qs, on, in, ta.left[in], few);
+            };
+            // what does not run in nodes: memories whole in LDS if they are
+            // few, else the work queue
+            auto general = [&](uint32_t in, hipStream_t on) {
+                uint32_t sh = 6;
+                while (2 * align_up(whole_lds_bytes(max_n, sh), kLdsGrain) > lds) --sh;
+                const uint64_t per_cu = std::min<uint64_t>(32, lds / align_up(whole_lds_bytes(max_n, sh), kLdsGrain));
+                const uint32_t waves_w = static_cast<uint32_t>(std::min<uint64_t>(total, per_cu * static_cast<uint64_t>(c->cus)));
+                ta.in = in;
+                ta.few = kWholeRounds * (waves_w << sh);
+                const uint32_t few = ta.few;
+                const hipError_t e = launch_whole(dt2, isa, pow2, wm, ta, sh, max_n, waves_w, qs, on);
+                if (e) return e;
+                return queue(in, P, wpb, blocks, few, on);
+            };
+            if ((rc = ensure_stream2(c))) return rc;
+            hipStream_t st2 = c->stream2;
+            // one span for all of them; the general list's part of it, on the
+            // second stream, also has its own
+            HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
+                hipError_t e = hipSuccess;
+                if (warm)
+                    e = launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
+                                          kTraceWarm - cap, ta.idx[kListWarm], qs, st);
+                if (!e) e = traces(from, kTraceNodes, kTraceData);
+                if (!e) e = hipEventRecord(c->ev_first, st);
+                if (!e) e = hipStreamWaitEvent(st2, c->ev_first, 0);
+                if (!e) e = timed_launch(c, RASP_KERNEL_MISFIT, [&] { return general(kListGeneral, st2); }, st2);
+                if (!e) e = hipEventRecord(c->ev_second, st2);
+                if (!e) e = traces(kListFull, kTraceNodes2, kTraceData2);
+                if (!e) e = general(kListLast, st);
+                if (!e) e = hipStreamWaitEvent(st, c->ev_second, 0);
+                if (!e) e = queue(kListEnd, 0u, 4u, std::max<uint32_t>(1, 8u * static_cast<uint32_t>(c->cus)), 0u, st);
+                return e; }));
+        } else {
+            HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
+                return launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
+                                         kNoCap, nullptr, qs, st); }));
+        }
         for (uint32_t t = 0; t < k; ++t) bs[t]->dev.fresh = 0;
     } else if (cap >= maxb && !lds_first) {
         HIPCHK(c, timed_launch(c, RASP_KERNEL_PLAIN, [&] {

@@ -1,0 +1,120 @@
+"""GPU parity of the trace kernel and of the lists it hands on, bit-exact.
+
+A persistent run with a first pass and a large enough budget compiles its
+survivors into nodes (k_trace), steps the rest whole in LDS (k_whole) or on the
+work queue.  Every field of every machine is compared with the oracle.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2604_12902_amd import workloads as W
+from test_gpu_parity import _boundary_programs, _image, _random_states, compare
+
+pytestmark = pytest.mark.gpu
+
+
+def _uniform(seed, num_vms, isa, n, w=32, m=12):
+    """Random programs of 2m words over opcodes 1..8 with operands near the
+    program, one n for all machines, two inputs and two outputs at most."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    words = rng.integers(-2, min(2 * m + 4, n + 3), (num_vms, 2 * m))
+    words[:, ::2] = rng.integers(1, 9, (num_vms, m))
+    words = words[:, :n]
+    b = W.from_programs(isa, [list(map(int, r)) for r in words], n, [[3, -4]] * num_vms, ell=2, s=2)
+    b.word_bits = w
+    return b
+
+
+def _wanderers(num_vms, n):
+    """Counted stores through a moving address that ends up in the program:
+    addresses new on every round, which no node holds."""
+    LOAD, ADD, STORE, JMP = 1, 2, 4, 8
+    progs = [_image(n, {0: LOAD, 1: k % 9, 2: STORE, 3: 24 + k % 700, 4: LOAD, 5: 0, 6: ADD, 7: 3, 8: ADD, 9: 20,
+                        10: STORE, 11: 3, 12: JMP, 13: 0, 20: 1 + 2 * (k % 3)}) for k in range(num_vms)]
+    return W.from_programs(W.ISA_CLASSIC, progs, n, [[]] * num_vms, ell=0, s=1)
+
+
+# budgets on both sides of the fewest transitions traces are compiled for
+# (2,048 after the first pass; 8,192 with memories whole in LDS)
+CASES = {
+    "classic-n7": (lambda: _uniform(1, 6000, 1, 7), dict(first_pass=4), 2051),
+    "classic-n1": (lambda: _uniform(2, 3000, 1, 1), dict(first_pass=4), 2052),
+    "classic-n2": (lambda: _uniform(3, 3000, 1, 2), dict(first_pass=4), 2053),
+    "classic-n64": (lambda: _uniform(4, 40000, 1, 64), dict(first_pass=4), 2052),
+    "word-n31": (lambda: _uniform(5, 40000, 0, 31), dict(first_pass=1), 5000),
+    "word-n64-lds64": (lambda: _uniform(6, 20000, 0, 64), dict(first_pass=16, lds_words=64), 8208),
+    "classic-n33-w8": (lambda: _uniform(7, 40000, 1, 33, w=8), dict(first_pass=600), 6000),
+    "word-n40-w29": (lambda: _uniform(8, 20000, 0, 40, w=29), dict(), 4096),
+    "boundaries": (lambda: W.from_programs(1, _boundary_programs(41) * 20, 41, [[3, -4]] * 100, ell=2, s=2),
+                   dict(first_pass=1), 9000),
+    "uneven": (lambda: W.config3(num_vms=6000, seed=9), dict(lds_words=40, first_pass=576), 20000),
+    "wanderers": (lambda: _wanderers(700, 1024), dict(first_pass=64), 7000),
+    # more of them than k_whole takes: the work queue steps them
+    "wanderers-many": (lambda: _wanderers(40000, 1024), dict(first_pass=64), 3500),
+}
+
+
+@pytest.fixture(scope="module")
+def R():
+    import torch
+    from paper_2604_12902_amd import rasp as R
+    assert torch.cuda.is_available()
+    return R
+
+
+def _context(R, knobs, nbytes=1 << 30):
+    c = R.Context(nbytes)
+    c.set(R.RASP_OPT_SCHEDULE, 2)
+    for k, v in knobs.items():
+        c.set({"first_pass": R.RASP_OPT_FIRST_PASS, "lds_words": R.RASP_OPT_LDS_WORDS}[k], v)
+    return c
+
+
+@pytest.mark.parametrize("case", list(CASES) + ["states-classic", "states-word", "runs", "multi", "no-room"])
+def test_traces_bit_exact(R, case):
+    print("case:", case, flush=True)
+    if case in CASES:
+        make, knobs, budget = CASES[case]
+        b = make()
+        with _context(R, knobs) as c:
+            h = c.load(b)
+            c.run(h, budget)
+            compare(c.fetch(h, mem=True), oracle.run(b, budget, threads=8, w=b.word_bits))
+    elif case.startswith("states"):
+        # i near INT32_MAX, odd, negative; a and memory at the int32 edges
+        isa = 1 if case == "states-classic" else 0
+        b = W.tiny_random(seed=50 + isa, num_vms=8000, isa=isa, max_m=6, max_n=30, max_ell=4, max_s=3, opcode_hi=10)
+        st = _random_states(b, seed=51 + isa)
+        with _context(R, dict(first_pass=2)) as c:
+            h = c.load_state(b, dict(i=st.i, a=st.a, u0=st.u0, y0=st.y0, steps=st.steps, y=st.Y, mem=st.mem))
+            c.run(h, 3000)
+            oracle.advance(st, 3000)
+            compare(c.fetch(h, mem=True), st)
+    elif case == "runs":
+        # one run's machines go on in the next
+        b = W.config3(num_vms=3000, seed=10)
+        with _context(R, dict(first_pass=100)) as c:
+            h = c.load(b)
+            for budget in (2500, 1, 2148, 4000):
+                c.run(h, budget)
+            compare(c.fetch(h, mem=True), oracle.run(b, 8649, threads=8))
+    elif case == "multi":
+        # several batches in one launch: the lists hold machines of all
+        bs = [W.config3(num_vms=1000 + 77 * k, seed=20 + k) for k in range(3)]
+        with _context(R, dict(first_pass=64)) as c:
+            hs = [c.load(b) for b in bs]
+            c.run_multi(hs, [6000, 2600, 6000])
+            for h, b, budget in zip(hs, bs, (6000, 2600, 6000)):
+                compare(c.fetch(h, mem=True), oracle.run(b, budget, threads=8))
+    else:
+        # an arena with room for the load (32 bytes a machine of staging) but not
+        # for the survivor list and the lists traces need (40 bytes): the run
+        # goes without them
+        progs = [[1, k % 5, 8, 0] if k % 3 else [1, 7, 4, 2] for k in range(1 << 20)]
+        b = W.from_programs(W.ISA_CLASSIC, progs, 32, ell=0, s=1)
+        room = R.rasp_batch_footprint(R.make_desc(b)) + 34 * b.N + (1 << 20)
+        with _context(R, dict(first_pass=4), room) as c:
+            h = c.load(b)
+            c.run(h, 2100)
+            compare(c.fetch(h), oracle.run(b, 2100, threads=8), mem=False)
