@@ -106,9 +106,17 @@ enum : uint32_t {
 struct TraceArgs {
     uint32_t NO, ND;                   // nodes and data words a lane
     uint32_t in;                       // the list this launch works on
-    uint32_t few;                      // k_whole: the longest list it takes
+    uint32_t few;                      // k_whole: the longest list it takes,
+    uint32_t spread;                   // the waves it spreads a short one over,
+    uint32_t slab;                     // the bytes of LDS of each,
+    uint32_t already;                  // and the first pass's transitions
     uint32_t *idx[7], *left[7];        // by list (left null: the budget less the first pass)
 };
+// Waves a block of k_trace (at most) and of k_whole.  One-wave blocks of a
+// launch of a few waves a CU land on one SIMD of each (k_whole, a loop of four
+// instructions: 143 ns a transition with 256 such blocks, 310 with 1,024); the
+// waves of one block are spread.
+constexpr uint32_t kTraceWpb = 8, kWholeWpb = 4;
 constexpr uint32_t kTraceMax = 8;      // transitions of a node at most
 constexpr uint32_t kTraceRounds = 16;  // general steps of a lane between runs of macro steps
 constexpr uint32_t kTraceNear = 32;    // macro steps before its end from which a lane waits for others,
@@ -180,9 +188,9 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
 // whole memories in LDS, 2^sh lanes a wave, over list ta.in if it has at
 // most ta.few machines
 hipError_t launch_whole(const BatchTable *tab, uint32_t isa, bool pow2, bool wm, const TraceArgs &ta, uint32_t sh,
-                        uint32_t max_n, uint32_t blocks, QueueState *q, hipStream_t st);
-hipError_t launch_trace(const BatchTable *tab, uint32_t already, uint32_t isa, bool wm, const TraceArgs &ta,
                         uint32_t blocks, QueueState *q, hipStream_t st);
+hipError_t launch_trace(const BatchTable *tab, uint32_t already, uint32_t isa, bool wm, const TraceArgs &ta,
+                        uint32_t wpb, uint32_t blocks, QueueState *q, hipStream_t st);
 // the persistent kernel over the fits of a hot-cell first pass, each
 // machine's hot cells in its lane's LDS table
 hipError_t launch_persistent_hot(const BatchTable *tab, const uint32_t *work, uint32_t already, uint32_t isa,

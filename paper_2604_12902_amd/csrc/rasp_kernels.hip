@@ -2120,23 +2120,38 @@ __device__ __forceinline__ bool trace_step(TraceTab &tr, Regs &r, const gi32 *T,
     return true;
 }
 
+// x of lane src
+template <class T>
+__device__ __forceinline__ T lane_of(T x, uint32_t src)
+{
+    return __shfl(x, static_cast<int>(src));
+}
+__device__ __forceinline__ gi32 *lane_of(gi32 *x, uint32_t src)
+{
+    return reinterpret_cast<gi32 *>(__shfl(reinterpret_cast<unsigned long long>(x), static_cast<int>(src)));
+}
+
 template <int ISA, bool WM>
-__global__ __launch_bounds__(kWave) void k_trace(const BatchTable *__restrict__ tab, uint32_t already, TraceArgs ta,
+__global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *__restrict__ tab, uint32_t already, TraceArgs ta,
                                                  QueueState *__restrict__ q)
 {
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wib = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave)));
+    const uint32_t wpb = blockDim.x / kWave;
     const uint64_t total = ta.in == kListFirst ? q->survivors : q->count[ta.in];
     unsigned long long *const head = ta.in == kListFirst ? &q->head : &q->next[ta.in];
     // few machines are spread over the launch's waves: a wave waits for
     // every lane that compiles or steps in general
-    const uint64_t share = (total + gridDim.x - 1u) / gridDim.x;
+    const uint64_t share = (total + gridDim.x * wpb - 1u) / (gridDim.x * wpb);
     const uint32_t lanes = static_cast<uint32_t>(share < 64u ? (share < 1u ? 1u : share) : 64u);
     TraceTab tr;
     tr.NO = ta.NO;
     tr.ND = ta.ND;
-    tr.nb = 16u * lane;
-    tr.db = (ta.NO << 10) + 4u * lane;
-    tr.kb = (ta.NO << 10) + ((ta.ND + 2u) << 8) + 2u * lane;
+    // the nodes of all waves, then each wave's other arrays
+    const uint32_t rest = (wpb * ta.NO << 10) + wib * (trace_lds_bytes(ta.NO, ta.ND) - (ta.NO << 10));
+    tr.nb = (wib * ta.NO << 10) + 16u * lane;
+    tr.db = rest + 4u * lane;
+    tr.kb = rest + ((ta.ND + 2u) << 8) + 2u * lane;
     tr.pb = tr.kb + (ta.NO << 7);
     tr.nn = tr.dn = tr.ev = tr.full = 0;
     tr.code = tr.keys = tr.held = tr.dirty = 0;
@@ -2268,10 +2283,15 @@ __global__ __launch_bounds__(kWave) void k_trace(const BatchTable *__restrict__ 
             if (steps > span) steps = span;
             if (wait && steps > 8u) steps = 8u;
             bool stubbed = false;
-            if (go) {
+            // a lane that does not go runs along with the first that does (as
+            // in k_whole; beaver 11.1 -> 7.7 ms, fig1's second launch 14.8 -> 11.0)
+            const uint64_t going = __ballot(go);
+            if (going != 0) {
+                const uint32_t src = go ? lane : static_cast<uint32_t>(__builtin_ctzll(going));
                 uint32_t acc = 0;
-                int32_t a = r.a;
-                v4i w = *reinterpret_cast<const lv4i *>(cur);
+                int32_t a = lane_of(r.a, src);
+                const uint32_t at = 16u * src, wsx = lane_of(ws, src);
+                v4i w = *reinterpret_cast<const lv4i *>(lane_of(cur, src));
 #pragma unroll 4
                 for (uint32_t t = steps; t != 0; --t) {
                     const uint32_t y = static_cast<uint32_t>(w[1]), z = static_cast<uint32_t>(w[2]);
@@ -2281,8 +2301,8 @@ __global__ __launch_bounds__(kWave) void k_trace(const BatchTable *__restrict__ 
                     // 167 cycles a step for one wave, 16.5 against 17.7 a
                     // step and CU with ten)
                     const int32_t d = lds_i32(y >> 14);
-                    const v4i wf = *reinterpret_cast<const lv4i *>(((nx & 0xffu) << 10) | (16u * lane));
-                    const v4i wt = *reinterpret_cast<const lv4i *>((__builtin_amdgcn_ubfe(nx, 8u, 8u) << 10) | (16u * lane));
+                    const v4i wf = *reinterpret_cast<const lv4i *>(((nx & 0xffu) << 10) | at);
+                    const v4i wt = *reinterpret_cast<const lv4i *>((__builtin_amdgcn_ubfe(nx, 8u, 8u) << 10) | at);
                     acc += y << 16;
                     const int32_t keep = static_cast<int32_t>(z << 31) >> 31, m = static_cast<int32_t>(z << 30) >> 31;
                     const uint32_t b = static_cast<uint32_t>(a & keep) + static_cast<uint32_t>(w[0]);
@@ -2293,7 +2313,7 @@ __global__ __launch_bounds__(kWave) void k_trace(const BatchTable *__restrict__ 
                         const uint32_t sum = b + static_cast<uint32_t>(d), mul = b * static_cast<uint32_t>(d);
                         x = (mul & static_cast<uint32_t>(m)) | (sum & ~static_cast<uint32_t>(m));
                     }
-                    a = WM ? sext(x, ws) : static_cast<int32_t>(x);
+                    a = WM ? sext(x, wsx) : static_cast<int32_t>(x);
                     lds_i32(z >> 14) = a;
                     // a > 0 as a - 1 < 2^31 - 1, or a != 0 as a - 1 < 2^32 - 1
                     const bool tk = ISA == 1 ? static_cast<uint32_t>(a) - 1u < ((z << 18) | 0x7fffffffu) : a != 0;
@@ -2302,10 +2322,12 @@ __global__ __launch_bounds__(kWave) void k_trace(const BatchTable *__restrict__ 
                     w[2] = tk ? wt[2] : wf[2];
                     w[3] = tk ? wt[3] : wf[3];
                 }
-                r.a = a;
-                left -= acc >> 16;
-                cur = tr.node((static_cast<uint32_t>(w[2]) >> 3) & 0xffu);
-                stubbed = (w[1] & 0xffff) == 0;
+                if (go) {
+                    r.a = a;
+                    left -= acc >> 16;
+                    cur = tr.node((static_cast<uint32_t>(w[2]) >> 3) & 0xffu);
+                    stubbed = (w[1] & 0xffff) == 0;
+                }
             }
             // stubs are looked for seldom once they are rare
             span = __ballot(stubbed) != 0 ? (span > 16u ? span >> 2 : 4u) : (span < 1024u ? span << 1 : span);
@@ -2337,10 +2359,13 @@ __global__ __launch_bounds__(kWave) void k_trace(const BatchTable *__restrict__ 
 // run in nodes.  Word k of lane l's memory is LDS word (k << sh) + l; word n
 // takes the stores that do not happen.  The lanes step in lockstep, so a wave
 // of few lanes takes a transition as fast as a full one, and memories of up
-// to 1,024 words fit.  A list of more than ta.few machines is left to the
+// to 2,048 words fit.  A list of more than ta.few machines is left to the
 // work queue.
-// A transition's bound is its chain at one wave a SIMD: some 35 vector
-// instructions and one LDS round trip.  The loop has one exit, at its end,
+// A transition's bound is its chain at one wave a SIMD: 36 vector instructions
+// and one LDS round trip, 113 ns (n a power of two; 145 otherwise), against
+// 226-330 ns in k_persistent's slots with the same machines: plain-scale's
+// survivors 0.91 -> 0.63 ms, ragged w = 16 1.38 -> 0.72, 1,024 tiny machines
+// 0.133 -> 0.080.  The loop has one exit, at its end,
 // where the next instruction is known: it goes on while that is common for
 // every lane (as in run_lockstep: no READ, append, HALT, jump onto itself or
 // counter near the largest word) and transitions are left.
@@ -2408,6 +2433,8 @@ __device__ __forceinline__ uint32_t run_whole(uint32_t base, const gi32 *T, gi32
             return ok;
         };
         uint32_t ok = decode();
+        // (a counter that is there already: i + 2 may have wrapped)
+        if (!POW2 || WM) ok = i > top ? 0u : ok;
         if (!any_lane(min(ok, left) == 0u)) {
             do {
                 const uint32_t nx = base + np * kWord;
@@ -2454,19 +2481,25 @@ __device__ __forceinline__ uint32_t run_whole(uint32_t base, const gi32 *T, gi32
 }
 
 template <int ISA, bool POW2, uint32_t SH>
-__global__ __launch_bounds__(kWave) void k_whole(const BatchTable *__restrict__ tab, TraceArgs ta, uint32_t wm,
+__global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *__restrict__ tab, TraceArgs ta, uint32_t wm,
                                                  QueueState *__restrict__ q)
 {
-    const uint32_t lane = threadIdx.x;
-    const uint64_t total = q->count[ta.in];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wib = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave)));
+    const uint32_t slab = wib * ta.slab;                 // the wave's LDS
+    const uint64_t total = ta.in == kListFirst ? q->survivors : q->count[ta.in];
     if (total > ta.few) return;
-    // as many a wave as spreads them over the launch, at most 2^SH
-    const uint64_t even = (total + gridDim.x - 1u) / gridDim.x;
-    const uint32_t share = static_cast<uint32_t>(even < (1u << SH) ? (even < 1u ? 1u : even) : (1u << SH));
+    unsigned long long *const head = ta.in == kListFirst ? &q->head : &q->next[ta.in];
+    // as few lanes a wave as one wave a SIMD allows, then more lanes, then
+    // more waves
+    const uint64_t need = (total + (1u << SH) - 1u) >> SH;
+    const uint32_t waves = static_cast<uint32_t>(min(static_cast<uint64_t>(gridDim.x) * kWholeWpb, max(need, static_cast<uint64_t>(ta.spread))));
+    if (blockIdx.x * kWholeWpb + wib >= waves) return;
+    const uint32_t share = static_cast<uint32_t>(min((total + waves - 1u) / waves, static_cast<uint64_t>(1u << SH)));
     for (;;) {
         unsigned long long first = 0;
-        if (lane == 0)
-            first = __hip_atomic_fetch_add(&q->next[ta.in], static_cast<unsigned long long>(share), __ATOMIC_RELAXED,
+        if (lane == 0 && share != 0)
+            first = __hip_atomic_fetch_add(head, static_cast<unsigned long long>(share), __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
         first = __shfl(first, 0);
         if (first >= total) break;
@@ -2490,20 +2523,37 @@ __global__ __launch_bounds__(kWave) void k_whole(const BatchTable *__restrict__ 
             M = gptr(bp->M + gany(bp->mem_off)[v]);
             T = gptr(bp->T + gany(bp->t_off)[v]);
             Y = gptr(bp->Y + gany(bp->y_off)[v]);
-            left = limit = ta.left[ta.in][item];
+            const uint32_t budget = tab->budget[k];
+            left = limit = ta.left[ta.in] ? ta.left[ta.in][item] : budget > ta.already ? budget - ta.already : 0u;
+            has = left != 0 && gany(bp->status)[v] == 0;
         }
         const uint32_t top = wave_max(has ? r.n : 0u);
         for (uint32_t k = 0; k < top; ++k)
-            if (has && k < r.n) dma4((const int32_t *)(M + k), k << SH);
+            if (has && k < r.n) dma4((const int32_t *)(M + k), slab / 4u + (k << SH));
         __builtin_amdgcn_s_waitcnt(0);
-        while (__ballot(has) != 0) {
+        for (uint64_t live; (live = __ballot(has)) != 0;) {
             const uint32_t L = wave_min(has ? left : ~0u);
+            // A lane without a machine runs along with the first that has one
+            // (the same LDS words, the same values, its results dropped):
+            // where four waves of a CU run, those with up to eight active
+            // lanes issue at less than half the rate (a loop of four
+            // instructions, 1,024 waves: 297 ns a transition with 1-8 lanes
+            // active, 116-120 with 9 or more, and with all 64 this way).
+            const uint32_t src = has ? lane : static_cast<uint32_t>(__builtin_ctzll(live));
+            Regs x = r;
+            x.n = lane_of(r.n, src); x.ell = lane_of(r.ell, src); x.s = lane_of(r.s, src);
+            x.i = lane_of(r.i, src); x.a = lane_of(r.a, src); x.p = lane_of(r.p, src);
+            x.u0 = lane_of(r.u0, src); x.y0 = lane_of(r.y0, src);
+            gi32 *const Tx = lane_of(T, src), *const Yx = lane_of(Y, src);
+            const uint32_t wsx = lane_of(ws, src), base = slab + 4u * src;
+            bool halted;
+            const uint32_t done = wm ? run_whole<ISA, POW2, true, SH>(base, Tx, Yx, x, L, halted, wsx)
+                                     : run_whole<ISA, POW2, false, SH>(base, Tx, Yx, x, L, halted, 0u);
             if (has) {
-                bool halted;
-                left -= wm ? run_whole<ISA, POW2, true, SH>(4u * lane, T, Y, r, L, halted, ws)
-                           : run_whole<ISA, POW2, false, SH>(4u * lane, T, Y, r, L, halted, 0u);
+                r = x;
+                left -= done;
                 if (halted || left == 0) {
-                    for (uint32_t k = 0; k < r.n; ++k) M[k] = lds_i32(4u * lane + (k << (SH + 2u)));
+                    for (uint32_t k = 0; k < r.n; ++k) M[k] = lds_i32(base + (k << (SH + 2u)));
                     gany(bp->i)[v] = r.i; gany(bp->a)[v] = r.a; gany(bp->u0)[v] = r.u0; gany(bp->y0)[v] = r.y0;
                     gany(bp->steps)[v] += limit - left;
                     if (halted) gany(bp->status)[v] = 1;
@@ -2518,18 +2568,19 @@ template <int ISA, bool POW2>
 static void whole_go(unsigned blocks, size_t shmem, hipStream_t st, const BatchTable *tab, const TraceArgs &ta, uint32_t sh,
                      uint32_t wm, QueueState *q)
 {
-    if (sh == 6u) k_whole<ISA, POW2, 6><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
-    else if (sh == 5u) k_whole<ISA, POW2, 5><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
-    else if (sh == 4u) k_whole<ISA, POW2, 4><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
-    else k_whole<ISA, POW2, 3><<<blocks, kWave, shmem, st>>>(tab, ta, wm, q);
+    if (sh == 6u) k_whole<ISA, POW2, 6><<<blocks, kWave * kWholeWpb, shmem, st>>>(tab, ta, wm, q);
+    else if (sh == 5u) k_whole<ISA, POW2, 5><<<blocks, kWave * kWholeWpb, shmem, st>>>(tab, ta, wm, q);
+    else if (sh == 4u) k_whole<ISA, POW2, 4><<<blocks, kWave * kWholeWpb, shmem, st>>>(tab, ta, wm, q);
+    else if (sh == 3u) k_whole<ISA, POW2, 3><<<blocks, kWave * kWholeWpb, shmem, st>>>(tab, ta, wm, q);
+    else k_whole<ISA, POW2, 2><<<blocks, kWave * kWholeWpb, shmem, st>>>(tab, ta, wm, q);
 }
 
 hipError_t launch_whole(const BatchTable *tab, uint32_t isa, bool pow2, bool wmb, const TraceArgs &ta, uint32_t sh,
-                        uint32_t max_n, uint32_t blocks, QueueState *q, hipStream_t st)
+                        uint32_t blocks, QueueState *q, hipStream_t st)
 {
-    const size_t shmem = whole_lds_bytes(max_n, sh);
+    const size_t shmem = kWholeWpb * static_cast<size_t>(ta.slab);
     const uint32_t wm = wmb ? 1u : 0u;
-    if (sh < 3u || sh > 6u) return hipErrorInvalidValue;
+    if (sh < 2u || sh > 6u) return hipErrorInvalidValue;
     if (isa == 1) {
         if (pow2) whole_go<1, true>(blocks, shmem, st, tab, ta, sh, wm, q);
         else whole_go<1, false>(blocks, shmem, st, tab, ta, sh, wm, q);
@@ -2548,10 +2599,11 @@ static void whole_attr()
 }
 
 hipError_t launch_trace(const BatchTable *tab, uint32_t already, uint32_t isa, bool wm, const TraceArgs &ta,
-                        uint32_t blocks, QueueState *q, hipStream_t st)
+                        uint32_t wpb, uint32_t blocks, QueueState *q, hipStream_t st)
 {
-    const dim3 grid(blocks), block(kWave);
-    const size_t shmem = trace_lds_bytes(ta.NO, ta.ND);
+    if (wpb == 0 || wpb > kTraceWpb || wpb * ta.NO > 255u) return hipErrorInvalidValue;
+    const dim3 grid(blocks), block(kWave * wpb);
+    const size_t shmem = wpb * static_cast<size_t>(trace_lds_bytes(ta.NO, ta.ND));
     if (isa == 1) {
         if (wm) k_trace<1, true><<<grid, block, shmem, st>>>(tab, already, ta, q);
         else k_trace<1, false><<<grid, block, shmem, st>>>(tab, already, ta, q);
@@ -2601,10 +2653,10 @@ void init_kernel_attributes()
     for (const void *k : {reinterpret_cast<const void *>(&k_trace<0, false>), reinterpret_cast<const void *>(&k_trace<0, true>),
                           reinterpret_cast<const void *>(&k_trace<1, false>), reinterpret_cast<const void *>(&k_trace<1, true>)})
         (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    whole_attr<0, false, 3>(); whole_attr<0, false, 4>(); whole_attr<0, false, 5>(); whole_attr<0, false, 6>();
-    whole_attr<0, true, 3>(); whole_attr<0, true, 4>(); whole_attr<0, true, 5>(); whole_attr<0, true, 6>();
-    whole_attr<1, false, 3>(); whole_attr<1, false, 4>(); whole_attr<1, false, 5>(); whole_attr<1, false, 6>();
-    whole_attr<1, true, 3>(); whole_attr<1, true, 4>(); whole_attr<1, true, 5>(); whole_attr<1, true, 6>();
+    whole_attr<0, false, 2>(); whole_attr<0, false, 3>(); whole_attr<0, false, 4>(); whole_attr<0, false, 5>(); whole_attr<0, false, 6>();
+    whole_attr<0, true, 2>(); whole_attr<0, true, 3>(); whole_attr<0, true, 4>(); whole_attr<0, true, 5>(); whole_attr<0, true, 6>();
+    whole_attr<1, false, 2>(); whole_attr<1, false, 3>(); whole_attr<1, false, 4>(); whole_attr<1, false, 5>(); whole_attr<1, false, 6>();
+    whole_attr<1, true, 2>(); whole_attr<1, true, 3>(); whole_attr<1, true, 4>(); whole_attr<1, true, 5>(); whole_attr<1, true, 6>();
     (void)hipGetLastError();
 }
 

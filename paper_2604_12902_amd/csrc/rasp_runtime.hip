@@ -32,6 +32,7 @@ static_assert(sizeof(BatchTable) >= 8 * kMaxMulti * kTickets, "device count slot
 constexpr uint32_t kTraceMinLeft = 2048, kTraceMinLeftLds = 8192;
 // transitions after which transients are over: traces start there
 constexpr uint32_t kTraceWarm = 512;
+constexpr uint32_t kWholeMaxN = 2048;     // largest memory k_whole takes (4 lanes a wave)
 constexpr uint32_t kWholeRounds = 2;      // times k_whole's lanes are filled at most
 constexpr uint64_t kLdsGrain = 1280;      // LDS of a block is taken in units of this
 constexpr uint64_t kStageWords = 32ull << 20;    // host-load staging: program + input words per chunk
@@ -881,6 +882,36 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
     const uint32_t S_hot = static_cast<uint32_t>(c->hot_cells);
     const bool hot = S_hot > 0 && sched == RASP_SCHED_PERSISTENT && cap > 0 && cap < maxb && !lds_first &&
                      !fused && max_n <= kHotMaxN && rs == nullptr;
+    // the machines of a list whole in LDS, one wave a SIMD, if they fill its
+    // lanes at most `rounds` times; `few`: the longest such list, which the work
+    // queue's launch then leaves alone (0: every list is the queue's)
+    uint32_t sh = 6;
+    while (sh > 2 && kWholeWpb * whole_lds_bytes(max_n, sh) > lds) --sh;
+    const uint32_t slab = whole_lds_bytes(max_n, sh);
+    const uint32_t blocks_w = static_cast<uint32_t>(std::min<uint64_t>(
+        (total + kWholeWpb - 1) / kWholeWpb,
+        std::min<uint64_t>(8, lds / align_up(kWholeWpb * slab, kLdsGrain)) * static_cast<uint64_t>(c->cus)));
+    const bool whole_ok = max_n <= kWholeMaxN;
+    auto whole = [&](const BatchTable *tb, TraceArgs wa, uint32_t in, uint32_t rounds, uint32_t *few, hipStream_t on) {
+        *few = whole_ok ? rounds * (kWholeWpb * blocks_w << sh) : 0;
+        if (!whole_ok) return hipSuccess;
+        wa.in = in;
+        wa.few = *few;
+        wa.spread = kWholeWpb * static_cast<uint32_t>(c->cus);
+        wa.slab = slab;
+        wa.already = cap;
+        return launch_whole(tb, isa, pow2, wm, wa, sh, blocks_w, qs, on);
+    };
+    // a first pass's survivors: whole in LDS if one round takes them all, else
+    // the work queue
+    auto survivors = [&](const BatchTable *tb, uint32_t *work) {
+        TraceArgs wa{};
+        wa.idx[kListFirst] = work;
+        uint32_t few;
+        const hipError_t e = whole(tb, wa, kListFirst, 1, &few, st);
+        return e ? e : launch_persistent(tb, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap,
+                                         nullptr, qs, st, kListFirst, nullptr, few);
+    };
     if (graphed) {
         // replay (capturing on first use) the launch sequence for this key
         std::vector<uint64_t> key;
@@ -905,10 +936,10 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             if (!e && cap > 0 && cap < maxb && lds_first) {
                 e = launch_persistent(gt, total, nullptr, 0, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, cap, work, qs, st);
                 if (!e) e = launch_reset_head(qs, st);
-                if (!e) e = launch_persistent(gt, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap, nullptr, qs, st);
+                if (!e) e = survivors(gt, work);
             } else if (!e && cap > 0 && cap < maxb) {
                 e = launch_plain(gt, total, cap, isa, pow2, false, wm, work, qs, st);
-                if (!e) e = launch_persistent(gt, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap, nullptr, qs, st);
+                if (!e) e = survivors(gt, work);
             } else if (!e && cap >= maxb && !lds_first) {
                 e = launch_plain(gt, total, maxb, isa, pow2, false, wm, nullptr, qs, st);
             } else if (!e) {
@@ -1028,9 +1059,9 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 ta.in = in;
                 ta.NO = NO;
                 ta.ND = ND;
-                const uint64_t per_cu = lds / align_up(trace_lds_bytes(NO, ND), kLdsGrain);
-                const uint64_t waves_t = std::min<uint64_t>(total, per_cu * static_cast<uint64_t>(c->cus));
-                return launch_trace(dt2, ran, isa, wm, ta, static_cast<uint32_t>(waves_t), qs, st);
+                const uint32_t wpb_t = static_cast<uint32_t>(std::min<uint64_t>(kTraceWpb, lds / trace_lds_bytes(NO, ND)));
+                const uint64_t blocks_t = std::min<uint64_t>((total + wpb_t - 1) / wpb_t, static_cast<uint64_t>(c->cus));
+                return launch_trace(dt2, ran, isa, wm, ta, wpb_t, static_cast<uint32_t>(blocks_t), qs, st);
             };
             auto queue = [&](uint32_t in, uint32_t Pw, uint32_t wpbw, uint32_t blocksw, uint32_t few, hipStream_t on) {
                 return launch_persistent(dt2, total, ta.idx[in], ran, isa, pow2, wm, epoch, Pw, max_n, max_ell, wpbw, blocksw,
@@ -1039,14 +1070,8 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             // what does not run in nodes: memories whole in LDS if they are
             // few, else the work queue
             auto general = [&](uint32_t in, hipStream_t on) {
-                uint32_t sh = 6;
-                while (2 * align_up(whole_lds_bytes(max_n, sh), kLdsGrain) > lds) --sh;
-                const uint64_t per_cu = std::min<uint64_t>(32, lds / align_up(whole_lds_bytes(max_n, sh), kLdsGrain));
-                const uint32_t waves_w = static_cast<uint32_t>(std::min<uint64_t>(total, per_cu * static_cast<uint64_t>(c->cus)));
-                ta.in = in;
-                ta.few = kWholeRounds * (waves_w << sh);
-                const uint32_t few = ta.few;
-                const hipError_t e = launch_whole(dt2, isa, pow2, wm, ta, sh, max_n, waves_w, qs, on);
+                uint32_t few;
+                const hipError_t e = whole(dt2, ta, in, kWholeRounds, &few, on);
                 if (e) return e;
                 return queue(in, P, wpb, blocks, few, on);
             };
@@ -1070,9 +1095,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 if (!e) e = queue(kListEnd, 0u, 4u, std::max<uint32_t>(1, 8u * static_cast<uint32_t>(c->cus)), 0u, st);
                 return e; }));
         } else {
-            HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
-                return launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
-                                         kNoCap, nullptr, qs, st); }));
+            HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] { return survivors(dt2, work); }));
         }
         for (uint32_t t = 0; t < k; ++t) bs[t]->dev.fresh = 0;
     } else if (cap >= maxb && !lds_first) {

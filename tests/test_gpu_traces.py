@@ -50,6 +50,13 @@ CASES = {
                    dict(first_pass=1), 9000),
     "uneven": (lambda: W.config3(num_vms=6000, seed=9), dict(lds_words=40, first_pass=576), 20000),
     "wanderers": (lambda: _wanderers(700, 1024), dict(first_pass=64), 7000),
+    # survivors that go to k_whole without traces: n of one to four lanes a wave,
+    # and one word more than it takes; more survivors than its lanes
+    "whole-n2048": (lambda: _wanderers(300, 2048), dict(first_pass=64), 4000),
+    "whole-n2049": (lambda: _wanderers(300, 2049), dict(first_pass=64), 4000),
+    "whole-n1": (lambda: _uniform(12, 1025, 1, 1), dict(first_pass=1), 700),
+    "whole-n250-w16": (lambda: _uniform(13, 30000, 0, 250, w=16), dict(first_pass=8, lds_words=252), 4000),
+    "whole-n1024-many": (lambda: _wanderers(9000, 1024), dict(first_pass=64), 1000),
     # more of them than k_whole takes: the work queue steps them
     "wanderers-many": (lambda: _wanderers(40000, 1024), dict(first_pass=64), 3500),
 }
@@ -71,7 +78,7 @@ def _context(R, knobs, nbytes=1 << 30):
     return c
 
 
-@pytest.mark.parametrize("case", list(CASES) + ["states-classic", "states-word", "runs", "multi", "no-room"])
+@pytest.mark.parametrize("case", list(CASES) + ["states-classic", "states-word", "runs", "multi", "no-room", "graph", "noalloc"])
 def test_traces_bit_exact(R, case):
     print("case:", case, flush=True)
     if case in CASES:
@@ -107,6 +114,16 @@ def test_traces_bit_exact(R, case):
             c.run_multi(hs, [6000, 2600, 6000])
             for h, b, budget in zip(hs, bs, (6000, 2600, 6000)):
                 compare(c.fetch(h, mem=True), oracle.run(b, budget, threads=8))
+    elif case in ("graph", "noalloc"):
+        # the survivors' launches captured, and without an allocation
+        b = _uniform(14, 20000, 1, 61)
+        with _context(R, dict(first_pass=8)) as c:
+            h = c.load(b)
+            c.set(R.RASP_OPT_GRAPH, 1 if case == "graph" else 0)
+            for k in range(3):
+                (c.run if case == "graph" else lambda x, y: R.rasp_run_noalloc(c.handle, x, y))(h, 1500)
+                c.sync(h)
+            compare(c.fetch(h, mem=True), oracle.run(b, 4500, threads=8))
     else:
         # an arena with room for the load (32 bytes a machine of staging) but not
         # for the survivor list and the lists traces need (40 bytes): the run
