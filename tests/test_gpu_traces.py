@@ -135,3 +135,18 @@ def test_traces_bit_exact(R, case):
             h = c.load(b)
             c.run(h, 2100)
             compare(c.fetch(h), oracle.run(b, 2100, threads=8), mem=False)
+
+
+# a load's waves walk 4 to 64 machines each, by the machines there are
+@pytest.mark.parametrize("num_vms", [1, 5, 63, (8 << 16) - 1, 8 << 16, (16 << 16) + 3])
+def test_load_groups_of_machines(R, num_vms):
+    print("case: load", num_vms, flush=True)
+    rng = np.random.Generator(np.random.PCG64(num_vms))
+    m = rng.integers(0, 5, num_vms)
+    words = rng.integers(-9, 9, int(2 * m.sum()), dtype=np.int32)
+    off = W._offsets(2 * m)
+    b = W.Batch(W.ISA_CLASSIC, words, off, rng.integers(8, 14, num_vms).astype(np.uint32), np.arange(num_vms, dtype=np.int32),
+                np.arange(num_vms + 1, dtype=np.uint64), np.ones(num_vms, np.uint32), np.ones(num_vms, np.uint32))
+    with R.Context(1 << 30) as c:
+        h = c.load(b)
+        compare(c.fetch(h, mem=True), oracle.run(b, 0))
