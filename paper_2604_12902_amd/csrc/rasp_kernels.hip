@@ -1820,6 +1820,7 @@ hipError_t launch_persistent_hot(const BatchTable *tab, const uint32_t *work, ui
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t kNone = ~0u;
+constexpr uint32_t kFewLanes = 8;       // active lanes a wave issues more slowly with
 
 // what a node without transitions stands for
 enum : uint32_t {
@@ -2219,64 +2220,97 @@ __global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *_
             continue;
         }
         // ---- bring every lane to a compiled node, or out of here ----
-        bool ready = false, halted = false, step = false;
+        bool ready = false, halted = false;
         uint32_t to = kNone;                                   // the list a machine leaves for (kListDone: none)
-        for (uint32_t round = 0; round < kTraceRounds; ++round) {
-            const bool want = has && !ready && to == kNone;
-            if (__ballot(want) == 0) break;
-            if (want) {
-                uint32_t slot = kNone;
-                int32_t c = 0;
-                if (left < kTraceMax * kTraceEnd) to = kListEnd;
-                if (cur != kNone) {
-                    const uint32_t x = (cur - tr.nb) >> 10;
-                    const uint32_t kd = tr.kind(x);
-                    ready = tr.transitions(x) != 0 && to == kNone;
-                    if (!ready) {                              // leave the node
-                        r.i = tr.at(x);
+        if (has && left < kTraceMax * kTraceEnd) to = kListEnd;
+        if (has && cur != kNone && to == kNone) ready = tr.transitions((cur - tr.nb) >> 10) != 0;
+        const bool own = has && !ready;
+        const uint64_t owns = __ballot(own);
+        if (owns != 0) {
+            // a few lanes compile or step in general: the others run along
+            // with them (as in the macro steps), with state of their own to
+            // throw away (beaver 7.25 -> 6.86 ms, uneven's launch 19.5 -> 19.0)
+            const uint32_t few = static_cast<uint32_t>(__popcll(owns));
+            uint32_t src = lane;
+            if (few <= kFewLanes) {
+                uint32_t k = 0;
+                for (uint64_t m = owns; m != 0; m &= m - 1ull, ++k)
+                    if (!own && lane % few == k) src = static_cast<uint32_t>(__builtin_ctzll(m));
+            }
+            TraceTab x = tr;
+            x.nb = lane_of(tr.nb, src); x.db = lane_of(tr.db, src); x.kb = lane_of(tr.kb, src); x.pb = lane_of(tr.pb, src);
+            x.nn = lane_of(tr.nn, src); x.dn = lane_of(tr.dn, src); x.ev = lane_of(tr.ev, src); x.full = lane_of(tr.full, src);
+            x.code = lane_of(tr.code, src); x.keys = lane_of(tr.keys, src); x.held = lane_of(tr.held, src);
+            x.dirty = lane_of(tr.dirty, src); x.M = lane_of(tr.M, src);
+            Regs z = r;
+            z.n = lane_of(r.n, src); z.ell = lane_of(r.ell, src); z.s = lane_of(r.s, src);
+            z.i = lane_of(r.i, src); z.a = lane_of(r.a, src); z.u0 = lane_of(r.u0, src); z.y0 = lane_of(r.y0, src);
+            gi32 *const Tx = lane_of(T, src), *const Yx = lane_of(Y, src);
+            const uint32_t limx = lane_of(limit, src), wsx = lane_of(ws, src);
+            const int32_t imaxx = lane_of(imax, src);
+            uint32_t curx = lane_of(cur, src), leftx = lane_of(left, src), readsx = lane_of(reads, src), tox = lane_of(to, src);
+            bool on = own || few <= kFewLanes, readyx = false, haltedx = false, step = false;
+            for (uint32_t round = 0; round < kTraceRounds; ++round) {
+                if (__ballot(on) == 0) break;
+                if (on) {
+                    uint32_t slot = kNone;
+                    int32_t c = 0;
+                    if (leftx < kTraceMax * kTraceEnd) tox = kListEnd;
+                    if (curx != kNone) {                       // leave the node
+                        const uint32_t k = (curx - x.nb) >> 10;
+                        const uint32_t kd = x.kind(k);
+                        z.i = x.at(k);
                         if (kd == kTrap) {
                             // the jump onto itself was counted: no
                             // transition but a fixed point
-                            ++left;
-                            halted = true;
-                            to = kListDone;
+                            ++leftx;
+                            haltedx = true;
+                            tox = kListDone;
                         } else if (kd == kMiss) {
                             // undo the test, step the STORE in general
-                            const uint32_t w = static_cast<uint32_t>(tr.M[tr.target(r.i, r.n)]) + static_cast<uint32_t>(r.a);
-                            r.a = WM ? sext(w, ws) : static_cast<int32_t>(w);
-                            ++left;
+                            const uint32_t w = static_cast<uint32_t>(x.M[x.target(z.i, z.n)]) + static_cast<uint32_t>(z.a);
+                            z.a = WM ? sext(w, wsx) : static_cast<int32_t>(w);
+                            ++leftx;
                             step = true;
                         } else if (kd == kKept) {
-                            r.a = c = tr.M[tr.target(r.i - 2, r.n)];
-                            slot = x;
+                            z.a = c = x.M[x.target(z.i - 2, z.n)];
+                            slot = k;
                         }
-                        cur = kNone;
+                        curx = kNone;
                     }
-                }
-                if (!ready && to == kNone) {
-                    uint32_t x = kNone;
-                    if (!step) x = trace_compile<ISA>(tr, r.i, r, imax, slot, c);
-                    step = false;
-                    const uint32_t done = limit - left;
-                    const bool often = tr.ev > kTraceEvents + (done >> 11);
-                    if (often || tr.full > kTraceFulls + (done >> 10)) {
-                        // (a kept word's value is in r.a already; a machine
-                        // whose i has left its memory never comes back to
-                        // the same i)
-                        if (often || static_cast<uint32_t>(r.i) >= r.n) to = ta.in == kListFull ? kListLast : kListGeneral;
-                        else to = ta.in == kListFull ? kListLast : kListFull;
-                    } else if (x != kNone) {
-                        cur = tr.node(x);
-                        ready = true;
-                    } else if (const uint32_t u = r.u0; trace_step<ISA, WM>(tr, r, T, Y, left, halted, ws, imax)) {
-                        // (a loop that reads a short tape ends with it soon)
-                        reads += r.u0 - u;
-                        if (r.u0 == u || reads > kTapeLdsMax) ++tr.ev;
-                        --left;
-                    } else {
-                        to = kListDone;
+                    if (tox == kNone) {
+                        uint32_t f = kNone;
+                        if (!step) f = trace_compile<ISA>(x, z.i, z, imaxx, slot, c);
+                        step = false;
+                        const uint32_t done = limx - leftx;
+                        const bool often = x.ev > kTraceEvents + (done >> 11);
+                        if (often || x.full > kTraceFulls + (done >> 10)) {
+                            // (a kept word's value is in a already; a machine
+                            // whose i has left its memory never comes back to
+                            // the same i)
+                            if (often || static_cast<uint32_t>(z.i) >= z.n) tox = ta.in == kListFull ? kListLast : kListGeneral;
+                            else tox = ta.in == kListFull ? kListLast : kListFull;
+                        } else if (f != kNone) {
+                            curx = x.node(f);
+                            readyx = true;
+                        } else if (const uint32_t u = z.u0; trace_step<ISA, WM>(x, z, Tx, Yx, leftx, haltedx, wsx, imaxx)) {
+                            // (a loop that reads a short tape ends with it soon)
+                            readsx += z.u0 - u;
+                            if (z.u0 == u || readsx > kTapeLdsMax) ++x.ev;
+                            --leftx;
+                        } else {
+                            tox = kListDone;
+                        }
                     }
+                    on = !readyx && tox == kNone;
                 }
+            }
+            if (own) {
+                tr = x;
+                r = z;
+                cur = curx; left = leftx; reads = readsx; to = tox;
+                ready = readyx;
+                halted = haltedx;
             }
         }
         // ---- run macro steps: until few transitions are left to some lane,
