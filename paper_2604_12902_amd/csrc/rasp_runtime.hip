@@ -1,6 +1,7 @@
 // rasp_runtime.hip -- host side of librasp: contexts, the device arena
 // sub-allocator, batch loading, run scheduling and output fetching behind the
 // C ABI of include/rasp.h.
+#include "rasp_hostcopy.h"
 #include "rasp_internal.h"
 #include "../../include/rasp.h"
 
@@ -204,6 +205,7 @@ struct rasp_ctx {
     uint64_t ticket_next = 1;            // ticket t uses slot t % kTickets
     uint64_t ticket_of[kTickets] = {};   // the ticket a slot holds (0: none)
     uint32_t ticket_k[kTickets] = {};
+    HostCopy host;                       // copies of pageable host memory
     // copy stream (same CU mask as the first): asynchronous fetches
     hipStream_t cstream = nullptr;
     // captured launch sequences (RASP_OPT_GRAPH)
@@ -463,8 +465,10 @@ int load_common(rasp_ctx *c, const rasp_batch_desc *d, std::unique_ptr<Batch> &o
             return bail(RASP_E_NOMEM);
         }
         carve_words(at<char>(c, B->words), B->sum_n_pad, B->sum_ell, &B->dev);
+        // (the stream is waited for after every chunk of machines below)
+        c->host.begin();
         auto H2D = [&](void *dst, const void *src, uint64_t bytes) {
-            return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
+            return c->host.put(c->device, dst, src, bytes, st);
         };
         hipError_t e = hipSuccess;
         if (!e) e = H2D(B->dev.n, h.n.data(), 4 * N);
@@ -530,6 +534,7 @@ int load_common(rasp_ctx *c, const rasp_batch_desc *d, std::unique_ptr<Batch> &o
             if (!e) e = timed_launch(c, RASP_KERNEL_PACK, [&] { return launch_pack(view, pg, po, pg, to, st); });
             // the staging buffer and the host offset vectors are reused: wait
             if (!e) e = hipStreamSynchronize(st);
+            c->host.begin();
             B->tails = true;
             v0 = v1;
         }
@@ -1266,6 +1271,7 @@ int rasp_destroy(rasp_ctx *c)
     (void)hipSetDevice(c->device);
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     if (c->cstream) (void)hipStreamSynchronize(c->cstream);
+    c->host.close();
     for (auto &g : c->graphs) if (g.exec) (void)hipGraphExecDestroy(g.exec);
     c->graphs.clear();
     for (int k = 0; k < kTableRing; ++k)
@@ -1359,15 +1365,21 @@ int rasp_load_state(rasp_ctx *c, const rasp_batch_desc *d, const rasp_outputs *s
         arena_free(c, &b.meta);
         return code;
     };
-    hipError_t e = hipMemcpyAsync(b.dev.i, s->i, 4 * N, kind, st);
-    if (!e) e = hipMemcpyAsync(b.dev.a, s->a, 4 * N, kind, st);
-    if (!e) e = hipMemcpyAsync(b.dev.u0, s->u0, 4 * N, kind, st);
-    if (!e) e = hipMemcpyAsync(b.dev.y0, s->y0, 4 * N, kind, st);
-    if (!e && s->steps) e = hipMemcpyAsync(b.dev.steps, s->steps, 8 * N, kind, st);
-    if (!e && s->y && b.sum_s) e = hipMemcpyAsync(b.dev.Y, s->y, 4 * b.sum_s, kind, st);
+    // (the stream is waited for before the call returns)
+    c->host.begin();
+    auto up = [&](void *dst, const void *src, uint64_t bytes) {
+        return kind == hipMemcpyHostToDevice ? c->host.put(c->device, dst, src, bytes, st)
+                                             : hipMemcpyAsync(dst, src, bytes, kind, st);
+    };
+    hipError_t e = up(b.dev.i, s->i, 4 * N);
+    if (!e) e = up(b.dev.a, s->a, 4 * N);
+    if (!e) e = up(b.dev.u0, s->u0, 4 * N);
+    if (!e) e = up(b.dev.y0, s->y0, 4 * N);
+    if (!e && s->steps) e = up(b.dev.steps, s->steps, 8 * N);
+    if (!e && s->y && b.sum_s) e = up(b.dev.Y, s->y, 4 * b.sum_s);
     if (e) { fail(c, RASP_E_DEVICE, "state copy: %s", hipGetErrorString(e)); return undo(RASP_E_DEVICE); }
     if (b.uniform_dense) {
-        e = hipMemcpyAsync(b.dev.M, s->mem, 4 * b.sum_n, kind, st);
+        e = c->host.copy(c->device, b.dev.M, s->mem, 4 * b.sum_n, kind, st);
     } else {
         // dense machine-major memory -> padded arena
         const uint64_t nsc = scan_scratch_words(N);
@@ -1378,7 +1390,7 @@ int rasp_load_state(rasp_ctx *c, const rasp_batch_desc *d, const rasp_outputs *s
         uint64_t *tot = at<uint64_t>(c, tmp, align_up(8 * N, kAlign) + align_up(8 * nsc, kAlign));
         int32_t *dense = at<int32_t>(c, tmp, align_up(8 * N, kAlign) + align_up(8 * nsc, kAlign) + kAlign);
         e = launch_scan_u32(b.dev.n, doff, N, sums, tot, st);
-        if (!e) e = hipMemcpyAsync(dense, s->mem, 4 * b.sum_n, kind, st);
+        if (!e) e = c->host.copy(c->device, dense, s->mem, 4 * b.sum_n, kind, st);
         if (!e) e = launch_scatter_words(dense, doff, b.dev.n, N, b.dev.M, b.dev.mem_off, st);
     }
     if (!e) e = launch_tails(b.dev, false, st);            // every memory word is stored
@@ -1541,19 +1553,25 @@ int rasp_fetch_outputs(rasp_ctx *c, rasp_batch h, const rasp_outputs *o)
     } else if ((rc = after_fetch(c, b))) {
         return rc;
     }
+    auto copy = [&](void *dst, const void *src, uint64_t bytes, hipMemcpyKind k, hipStream_t on) {
+        return async || k != hipMemcpyDeviceToHost ? hipMemcpyAsync(dst, src, bytes, k, on)
+                                                   : c->host.get(c->device, dst, src, bytes, on);
+    };
+    if (!async) c->host.begin();
+    Alloc digests;
     if (kind == hipMemcpyDeviceToDevice) {
         if (o->status || o->steps || o->i || o->a || o->u0 || o->y0)
             HIPCHK(c, timed_launch(c, RASP_KERNEL_OTHER, [&] {
                 return launch_fetch_scalars(b->dev, o->status, o->steps, o->i, o->a, o->u0, o->y0, st); }, st));
     } else {
-        if (o->status) HIPCHK(c, hipMemcpyAsync(o->status, b->dev.status, N, kind, st));
-        if (o->steps) HIPCHK(c, hipMemcpyAsync(o->steps, b->dev.steps, 8 * N, kind, st));
-        if (o->i) HIPCHK(c, hipMemcpyAsync(o->i, b->dev.i, 4 * N, kind, st));
-        if (o->a) HIPCHK(c, hipMemcpyAsync(o->a, b->dev.a, 4 * N, kind, st));
-        if (o->u0) HIPCHK(c, hipMemcpyAsync(o->u0, b->dev.u0, 4 * N, kind, st));
-        if (o->y0) HIPCHK(c, hipMemcpyAsync(o->y0, b->dev.y0, 4 * N, kind, st));
+        if (o->status) HIPCHK(c, copy(o->status, b->dev.status, N, kind, st));
+        if (o->steps) HIPCHK(c, copy(o->steps, b->dev.steps, 8 * N, kind, st));
+        if (o->i) HIPCHK(c, copy(o->i, b->dev.i, 4 * N, kind, st));
+        if (o->a) HIPCHK(c, copy(o->a, b->dev.a, 4 * N, kind, st));
+        if (o->u0) HIPCHK(c, copy(o->u0, b->dev.u0, 4 * N, kind, st));
+        if (o->y0) HIPCHK(c, copy(o->y0, b->dev.y0, 4 * N, kind, st));
     }
-    if (o->y && b->sum_s) HIPCHK(c, hipMemcpyAsync(o->y, b->dev.Y, 4 * b->sum_s, kind, st));
+    if (o->y && b->sum_s) HIPCHK(c, copy(o->y, b->dev.Y, 4 * b->sum_s, kind, st));
     Alloc tmp;
     if (o->mem_digest) {
         if (kind == hipMemcpyDeviceToDevice) {
@@ -1567,17 +1585,19 @@ int rasp_fetch_outputs(rasp_ctx *c, rasp_batch h, const rasp_outputs *o)
             HIPCHK(c, timed_launch(c, RASP_KERNEL_DIGEST, [&] { return launch_digest(b->dev, dd, st); }, st));
             HIPCHK(c, hipMemcpyAsync(o->mem_digest, dd, 8 * N, kind, st));
         } else {
-            if (!arena_alloc(c, 8 * N, &tmp)) return fail(c, RASP_E_NOMEM, "arena cannot hold digests");
-            HIPCHK(c, timed_launch(c, RASP_KERNEL_DIGEST, [&] { return launch_digest(b->dev, at<uint64_t>(c, tmp), st); }));
-            HIPCHK(c, hipMemcpyAsync(o->mem_digest, at<uint64_t>(c, tmp), 8 * N, kind, st));
-            HIPCHK(c, hipStreamSynchronize(st));
-            arena_free(c, &tmp);
+            if (!arena_alloc(c, 8 * N, &digests)) return fail(c, RASP_E_NOMEM, "arena cannot hold digests");
+            HIPCHK(c, timed_launch(c, RASP_KERNEL_DIGEST, [&] { return launch_digest(b->dev, at<uint64_t>(c, digests), st); }));
+            HIPCHK(c, copy(o->mem_digest, at<uint64_t>(c, digests), 8 * N, kind, st));
+            if (o->mem) {
+                HIPCHK(c, c->host.flush(st));
+                arena_free(c, &digests);
+            }
         }
     }
     if (o->mem) {
         if ((rc = store_tails(c, b))) return rc;
         if (b->uniform_dense) {
-            HIPCHK(c, hipMemcpyAsync(o->mem, b->dev.M, 4 * b->sum_n, kind, st));
+            HIPCHK(c, copy(o->mem, b->dev.M, 4 * b->sum_n, kind, st));
         } else {
             // padded arena -> dense machine-major, through an arena buffer
             const uint64_t nsc = scan_scratch_words(N);
@@ -1593,8 +1613,8 @@ int rasp_fetch_outputs(rasp_ctx *c, rasp_batch h, const rasp_outputs *o)
             HIPCHK(c, launch_scan_u32(b->dev.n, doff, N, sums, tot, st));
             HIPCHK(c, launch_gather_words(b->dev.M, b->dev.mem_off, b->dev.n, N, dense, doff, st));
             if (kind != hipMemcpyDeviceToDevice)
-                HIPCHK(c, hipMemcpyAsync(o->mem, dense, 4 * b->sum_n, kind, st));
-            HIPCHK(c, hipStreamSynchronize(st));
+                HIPCHK(c, copy(o->mem, dense, 4 * b->sum_n, kind, st));
+            HIPCHK(c, async ? hipStreamSynchronize(st) : c->host.flush(st));
             arena_free(c, &tmp);
         }
     }
@@ -1603,7 +1623,8 @@ int rasp_fetch_outputs(rasp_ctx *c, rasp_batch h, const rasp_outputs *o)
         b->fetch_pending = true;
         return RASP_OK;
     }
-    HIPCHK(c, hipStreamSynchronize(st));
+    HIPCHK(c, c->host.flush(st));
+    arena_free(c, &digests);
     return RASP_OK;
 }
 

@@ -150,3 +150,29 @@ def test_load_groups_of_machines(R, num_vms):
     with R.Context(1 << 30) as c:
         h = c.load(b)
         compare(c.fetch(h, mem=True), oracle.run(b, 0))
+
+
+# copies of host arrays below, at and above the sizes from which they go in
+# chunks (512 KiB) and by way of the pinned area (256 KiB, 1 MiB in all)
+@pytest.mark.parametrize("num_vms,n", [(64, 1024), (65537, 1), (131071, 1), (128, 1025), (3 << 18, 1), (10001, 1021)])
+def test_state_round_trip_by_size(R, num_vms, n):
+    print("case: round trip", num_vms, n, flush=True)
+    rng = np.random.Generator(np.random.PCG64(num_vms + n))
+    b = W.Batch(W.ISA_CLASSIC, np.zeros(0, np.int32), np.zeros(num_vms + 1, np.uint64), np.full(num_vms, n, np.uint32),
+                np.zeros(0, np.int32), np.zeros(num_vms + 1, np.uint64), np.ones(num_vms, np.uint32),
+                np.full(num_vms, 2, np.uint32))
+    st = oracle.init(b)
+    for k in ("i", "a"):
+        setattr(st, k, rng.integers(-2 ** 31, 2 ** 31, num_vms).astype(np.int32))
+    st.mem = rng.integers(-2 ** 31, 2 ** 31, st.mem.size).astype(np.int32)
+    st.Y = rng.integers(-9, 9, st.Y.size).astype(np.int32)
+    st.steps = rng.integers(0, 1000, num_vms).astype(np.uint64)
+    with R.Context(1 << 30) as c:
+        for _ in range(2):
+            h = c.load_state(b, dict(i=st.i, a=st.a, u0=st.u0, y0=st.y0, steps=st.steps, y=st.Y, mem=st.mem))
+            got = c.fetch(h, mem=True, digest=True)
+            c.free(h)
+            want = st.copy()
+            oracle.advance(want, 0)
+            compare(got, want)
+            assert np.array_equal(got["mem_digest"], oracle.digest(want))
