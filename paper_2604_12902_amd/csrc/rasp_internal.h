@@ -66,8 +66,8 @@ struct QueueState {
     unsigned long long misfits;        // hot-cell first pass: survivors whose hot cells do not all fit
     unsigned long long head_m;         // next unclaimed misfit
     unsigned long long pad2[2];
-    unsigned long long count[8];       // traces: machines in each list,
-    unsigned long long next[8];        // and the next unclaimed one
+    unsigned long long count[10];       // traces: machines in each list,
+    unsigned long long next[10];        // and the next unclaimed one
 };
 
 // Hot-cell tables.  A first pass profiles the last R transitions of every
@@ -98,19 +98,27 @@ enum : uint32_t {
     kListWarm = 2,                     // survivors of a second pass, where the first was short
     kListGeneral = 3,                  // not for nodes: k_whole, or the work queue if they are many
     kListFull = 4,                     // need larger tables
-    kListLast = 5,                     // as kListGeneral, of the machines with larger tables
-    kListEnd = 6,                      // near the end of their budget
-    kListDone = 7,                     // (no list: finished)
-    kLists = 8
+    kListMain = 5,                     // run in nodes
+    kListLast = 6,                     // of kListFull, not for nodes
+    kListLate = 7,                     // of kListMain, seen late not to fit or to step in general often
+    kListEnd = 8,                      // near the end of their budget
+    kListDone = 9,                     // (no list: finished)
+    kLists = 10
 };
 struct TraceArgs {
     uint32_t NO, ND;                   // nodes and data words a lane
     uint32_t in;                       // the list this launch works on
+    // k_trace: where machines go that step in general too often, that fill
+    // their tables too often, and (stop > 0) that have run `stop` transitions
+    uint32_t often, full, rest, stop;
+    uint32_t events, events_sh;        // how often: events general steps and one in 2^events_sh transitions
+    uint32_t fulls, fulls_sh;
+    uint32_t dense, least;             // machines a wave (0: as few as spread them over the launch), on `least` blocks at least
     uint32_t few;                      // k_whole: the longest list it takes,
     uint32_t spread;                   // the waves it spreads a short one over,
     uint32_t slab;                     // the bytes of LDS of each,
     uint32_t already;                  // and the first pass's transitions
-    uint32_t *idx[7], *left[7];        // by list (left null: the budget less the first pass)
+    uint32_t *idx[9], *left[9];       // by list (left null: the budget less the first pass)
 };
 // Waves a block of k_trace (at most) and of k_whole.  One-wave blocks of a
 // launch of a few waves a CU land on one SIMD of each (k_whole, a loop of four
@@ -121,8 +129,15 @@ constexpr uint32_t kTraceMax = 8;      // transitions of a node at most
 constexpr uint32_t kTraceRounds = 16;  // general steps of a lane between runs of macro steps
 constexpr uint32_t kTraceNear = 32;    // macro steps before its end from which a lane waits for others,
 constexpr uint32_t kTraceEnd = 1;      // and from which its machine leaves
-constexpr uint32_t kTraceEvents = 24;  // general steps (and one in 2,048 transitions) before a machine leaves
-constexpr uint32_t kTraceFulls = 2;    // times its tables are full (and once in 1,024) before it leaves
+// Sorted survivors run kTraceSort transitions first, transients among them,
+// which shows nearly all that do not run in small tables.
+constexpr uint32_t kTraceSort = 512;
+constexpr uint32_t kSortEvents = 64, kSortFulls = 4;         // as kTraceEvents and kTraceFulls, meanwhile
+constexpr uint32_t kTraceEvents = 24, kTraceEventsSh = 11;   // general steps (and one in 2^Sh transitions) before a machine leaves
+constexpr uint32_t kTraceFulls = 2, kTraceFullsSh = 10;      // times its tables are full before it leaves
+constexpr uint32_t kLateEvents = 64, kLateEventsSh = 8;      // the same for kListLate
+constexpr uint32_t kLateFulls = 16, kLateFullsSh = 9;
+constexpr uint32_t kTraceDense = 4;                          // machines a wave of those beside the rest
 constexpr uint32_t kTraceNodes = 16, kTraceData = 10;        // 7 waves a CU
 constexpr uint32_t kTraceNodes2 = 48, kTraceData2 = 40;      // 2 waves a CU
 // The largest memory traces are compiled for.  Positions would do to 2^15, but

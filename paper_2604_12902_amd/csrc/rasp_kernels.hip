@@ -2149,9 +2149,16 @@ __global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *_
     const uint32_t wpb = blockDim.x / kWave;
     const uint64_t total = ta.in == kListFirst ? q->survivors : q->count[ta.in];
     unsigned long long *const head = ta.in == kListFirst ? &q->head : &q->next[ta.in];
-    // few machines are spread over the launch's waves: a wave waits for
-    // every lane that compiles or steps in general
-    const uint64_t share = (total + gridDim.x * wpb - 1u) / (gridDim.x * wpb);
+    // few machines are spread over the launch's waves (a wave waits for every
+    // lane that compiles or steps in general), or over as many as `dense` a
+    // wave needs, where other launches run beside this one
+    uint32_t waves = gridDim.x * wpb;
+    if (ta.dense != 0) {
+        waves = static_cast<uint32_t>(min(static_cast<uint64_t>(waves),
+                                          max(static_cast<uint64_t>(ta.least) * wpb, (total + ta.dense - 1u) / ta.dense)));
+        if (blockIdx.x * wpb + wib >= waves) return;
+    }
+    const uint64_t share = (total + waves - 1u) / waves;
     const uint32_t lanes = static_cast<uint32_t>(share < 64u ? (share < 1u ? 1u : share) : 64u);
     TraceTab tr;
     tr.NO = ta.NO;
@@ -2223,6 +2230,7 @@ __global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *_
         bool ready = false, halted = false;
         uint32_t to = kNone;                                   // the list a machine leaves for (kListDone: none)
         if (has && left < kTraceMax * kTraceEnd) to = kListEnd;
+        else if (has && ta.stop != 0 && limit - left + kTraceMax > ta.stop) to = ta.rest;
         if (has && cur != kNone && to == kNone) ready = tr.transitions((cur - tr.nb) >> 10) != 0;
         const bool own = has && !ready;
         const uint64_t owns = __ballot(own);
@@ -2283,13 +2291,12 @@ __global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *_
                         if (!step) f = trace_compile<ISA>(x, z.i, z, imaxx, slot, c);
                         step = false;
                         const uint32_t done = limx - leftx;
-                        const bool often = x.ev > kTraceEvents + (done >> 11);
-                        if (often || x.full > kTraceFulls + (done >> 10)) {
+                        const bool often = x.ev > ta.events + (done >> ta.events_sh);
+                        if (often || x.full > ta.fulls + (done >> ta.fulls_sh)) {
                             // (a kept word's value is in a already; a machine
                             // whose i has left its memory never comes back to
                             // the same i)
-                            if (often || static_cast<uint32_t>(z.i) >= z.n) tox = ta.in == kListFull ? kListLast : kListGeneral;
-                            else tox = ta.in == kListFull ? kListLast : kListFull;
+                            tox = often || static_cast<uint32_t>(z.i) >= z.n ? ta.often : ta.full;
                         } else if (f != kNone) {
                             curx = x.node(f);
                             readyx = true;
@@ -2315,13 +2322,14 @@ __global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *_
         }
         // ---- run macro steps: until few transitions are left to some lane,
         // which then waits for others to come as far ----
-        const bool near = ready && left < kTraceMax * kTraceNear;
+        const bool near = ready && ta.stop == 0 && left < kTraceMax * kTraceNear;
         const uint64_t far_m = __ballot(ready && !near), near_m = __ballot(near);
         const bool tail = far_m == 0 || 4u * static_cast<uint32_t>(__popcll(near_m)) >= lanes;
         const bool go = ready && (tail || !near);
         if ((far_m | near_m) != 0) {
             const bool wait = __ballot(has && !ready && to == kNone) != 0;
-            uint32_t steps = wave_min(go ? left / kTraceMax : ~0u);
+            const uint32_t until = ta.stop != 0 ? min(left, ta.stop - (limit - left)) : left;
+            uint32_t steps = wave_min(go ? until / kTraceMax : ~0u);
             if (steps > span) steps = span;
             if (wait && steps > 8u) steps = 8u;
             bool stubbed = false;

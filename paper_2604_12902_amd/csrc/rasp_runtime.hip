@@ -33,6 +33,7 @@ static_assert(sizeof(BatchTable) >= 8 * kMaxMulti * kTickets, "device count slot
 constexpr uint32_t kTraceMinLeft = 2048, kTraceMinLeftLds = 8192;
 // transitions after which transients are over: traces start there
 constexpr uint32_t kTraceWarm = 512;
+constexpr uint32_t kSortMaxN = 512;       // largest memory for which survivors are sorted first
 constexpr uint32_t kWholeMaxN = 2048;     // largest memory k_whole takes (4 lanes a wave)
 constexpr uint32_t kWholeRounds = 2;      // times k_whole's lanes are filled at most
 constexpr uint64_t kLdsGrain = 1280;      // LDS of a block is taken in units of this
@@ -185,6 +186,9 @@ struct rasp_ctx {
     // misfits' launch runs there beside the fits' launch
     hipStream_t stream2 = nullptr;
     hipEvent_t ev_first = nullptr, ev_second = nullptr;
+    // third stream: the machines that need large tables
+    hipStream_t stream3 = nullptr;
+    hipEvent_t ev_third = nullptr;
     std::vector<uint32_t> cu_mask;       // empty: the context's stream has no CU mask
     // scratch: queue counters, batch tables (device ring + pinned host ring)
     Alloc scratch;
@@ -682,7 +686,7 @@ bool ensure_trace(rasp_ctx *c, uint64_t items)
         arena_free(c, &c->trace);
     }
     c->trace_cap = 0;
-    if (!arena_alloc(c, 9 * align_up(4 * items, kAlign), &c->trace)) return false;
+    if (!arena_alloc(c, 13 * align_up(4 * items, kAlign), &c->trace)) return false;
     c->trace_cap = items;
     return true;
 }
@@ -717,6 +721,18 @@ int ensure_stream2(rasp_ctx *c)
     if (!e) e = hipEventCreateWithFlags(&c->ev_first, hipEventDisableTiming);
     if (!e) e = hipEventCreateWithFlags(&c->ev_second, hipEventDisableTiming);
     if (e) return fail(c, RASP_E_DEVICE, "second stream: %s", hipGetErrorString(e));
+    return RASP_OK;
+}
+
+int ensure_stream3(rasp_ctx *c)
+{
+    if (c->stream3) return RASP_OK;
+    hipError_t e = c->cu_mask.empty()
+                       ? hipStreamCreateWithFlags(&c->stream3, hipStreamNonBlocking)
+                       : hipExtStreamCreateWithCUMask(&c->stream3, static_cast<uint32_t>(c->cu_mask.size()),
+                                                      c->cu_mask.data());
+    if (!e) e = hipEventCreateWithFlags(&c->ev_third, hipEventDisableTiming);
+    if (e) return fail(c, RASP_E_DEVICE, "third stream: %s", hipGetErrorString(e));
     return RASP_OK;
 }
 
@@ -1053,20 +1069,32 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             uint64_t part = 0;
             ta.idx[kListFirst] = work;
             ta.idx[kListWarm] = at<uint32_t>(c, c->trace, part++ * list);
-            for (uint32_t l : {kListGeneral, kListFull, kListLast, kListEnd}) {
+            for (uint32_t l : {kListGeneral, kListFull, kListMain, kListLast, kListLate, kListEnd}) {
                 ta.idx[l] = at<uint32_t>(c, c->trace, part++ * list);
                 ta.left[l] = at<uint32_t>(c, c->trace, part++ * list);
             }
-            // transients first: another pass, over the survivors
-            const bool warm = cap < kTraceWarm && maxb > kTraceWarm;
+            // Small memories: the survivors are sorted first, and what does not
+            // run in small tables runs beside the rest, on the CUs its launch
+            // leaves (fig1: 14.2 ms beside 11.1 and 10.4, one after the other
+            // 25.9 -> 15.9 ms a pass; beaver, with few such machines, 7.5
+            // either way).  Larger memories: k_whole's list takes the chip by
+            // itself (32 machines a CU at n = 1,024), so it and what the main
+            // launch finds late come after it (sorted, uneven 4M 64 ms against
+            // 54, uneven 50K 6.2-7.8 against 5.3).
+            // Not sorted, the transients go first, in a pass over the survivors.
+            const bool sort = max_n <= kSortMaxN;
+            const bool warm = !sort && cap < kTraceWarm && maxb > kTraceWarm;
             const uint32_t from = warm ? kListWarm : kListFirst, ran = warm ? kTraceWarm : cap;
-            auto traces = [&](uint32_t in, uint32_t NO, uint32_t ND) {
+            const uint32_t cus = static_cast<uint32_t>(c->cus);
+            auto traces = [&](uint32_t in, bool large, uint32_t often, uint32_t full, uint32_t on_cus, hipStream_t on) {
                 ta.in = in;
-                ta.NO = NO;
-                ta.ND = ND;
-                const uint32_t wpb_t = static_cast<uint32_t>(std::min<uint64_t>(kTraceWpb, lds / trace_lds_bytes(NO, ND)));
-                const uint64_t blocks_t = std::min<uint64_t>((total + wpb_t - 1) / wpb_t, static_cast<uint64_t>(c->cus));
-                return launch_trace(dt2, ran, isa, wm, ta, wpb_t, static_cast<uint32_t>(blocks_t), qs, st);
+                ta.NO = large ? kTraceNodes2 : kTraceNodes;
+                ta.ND = large ? kTraceData2 : kTraceData;
+                ta.often = often;
+                ta.full = full;
+                const uint32_t wpb_t = static_cast<uint32_t>(std::min<uint64_t>(kTraceWpb, lds / trace_lds_bytes(ta.NO, ta.ND)));
+                const uint64_t blocks_t = std::min<uint64_t>((total + wpb_t - 1) / wpb_t, on_cus);
+                return launch_trace(dt2, ran, isa, wm, ta, wpb_t, static_cast<uint32_t>(blocks_t), qs, on);
             };
             auto queue = [&](uint32_t in, uint32_t Pw, uint32_t wpbw, uint32_t blocksw, uint32_t few, hipStream_t on) {
                 return launch_persistent(dt2, total, ta.idx[in], ran, isa, pow2, wm, epoch, Pw, max_n, max_ell, wpbw, blocksw,
@@ -1080,8 +1108,8 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 if (e) return e;
                 return queue(in, P, wpb, blocks, few, on);
             };
-            if ((rc = ensure_stream2(c))) return rc;
-            hipStream_t st2 = c->stream2;
+            if ((rc = ensure_stream2(c)) || (rc = ensure_stream3(c))) return rc;
+            hipStream_t st2 = c->stream2, st3 = c->stream3;
             // one span for all of them; the general list's part of it, on the
             // second stream, also has its own
             HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
@@ -1089,15 +1117,44 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 if (warm)
                     e = launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
                                           kTraceWarm - cap, ta.idx[kListWarm], qs, st);
-                if (!e) e = traces(from, kTraceNodes, kTraceData);
-                if (!e) e = hipEventRecord(c->ev_first, st);
-                if (!e) e = hipStreamWaitEvent(st2, c->ev_first, 0);
-                if (!e) e = timed_launch(c, RASP_KERNEL_MISFIT, [&] { return general(kListGeneral, st2); }, st2);
-                if (!e) e = hipEventRecord(c->ev_second, st2);
-                if (!e) e = traces(kListFull, kTraceNodes2, kTraceData2);
-                if (!e) e = general(kListLast, st);
-                if (!e) e = hipStreamWaitEvent(st, c->ev_second, 0);
-                if (!e) e = queue(kListEnd, 0u, 4u, std::max<uint32_t>(1, 8u * static_cast<uint32_t>(c->cus)), 0u, st);
+                ta.events = sort ? kSortEvents : kTraceEvents; ta.events_sh = kTraceEventsSh;
+                ta.fulls = sort ? kSortFulls : kTraceFulls; ta.fulls_sh = kTraceFullsSh;
+                if (sort) {
+                    ta.rest = kListMain;
+                    ta.stop = kTraceSort;
+                    if (!e) e = traces(from, false, kListGeneral, kListFull, cus, st);
+                    ta.stop = 0;
+                    ta.events = kTraceEvents;
+                    ta.fulls = kTraceFulls;
+                    if (!e) e = hipEventRecord(c->ev_first, st);
+                    if (!e) e = hipStreamWaitEvent(st2, c->ev_first, 0);
+                    if (!e) e = hipStreamWaitEvent(st3, c->ev_first, 0);
+                    if (!e) e = timed_launch(c, RASP_KERNEL_MISFIT, [&] { return general(kListGeneral, st2); }, st2);
+                    if (!e) e = hipEventRecord(c->ev_second, st2);
+                    ta.dense = kTraceDense;
+                    if (!e) e = traces(kListFull, true, kListLast, kListLast, cus, st3);
+                    if (!e) e = general(kListLast, st3);
+                    if (!e) e = hipEventRecord(c->ev_third, st3);
+                    // (5/8 of the CUs hold 71,680 machines)
+                    ta.dense = kWave;
+                    ta.least = cus * 5 / 8;
+                    ta.events = kLateEvents; ta.events_sh = kLateEventsSh;
+                    ta.fulls = kLateFulls; ta.fulls_sh = kLateFullsSh;
+                    if (!e) e = traces(kListMain, false, kListLate, kListLate, cus - cus / 8, st);
+                    if (!e) e = hipStreamWaitEvent(st, c->ev_second, 0);
+                    if (!e) e = hipStreamWaitEvent(st, c->ev_third, 0);
+                    if (!e) e = general(kListLate, st);
+                } else {
+                    if (!e) e = traces(from, false, kListGeneral, kListFull, cus, st);
+                    if (!e) e = hipEventRecord(c->ev_first, st);
+                    if (!e) e = hipStreamWaitEvent(st2, c->ev_first, 0);
+                    if (!e) e = timed_launch(c, RASP_KERNEL_MISFIT, [&] { return general(kListGeneral, st2); }, st2);
+                    if (!e) e = hipEventRecord(c->ev_second, st2);
+                    if (!e) e = traces(kListFull, true, kListLast, kListLast, cus, st);
+                    if (!e) e = general(kListLast, st);
+                    if (!e) e = hipStreamWaitEvent(st, c->ev_second, 0);
+                }
+                if (!e) e = queue(kListEnd, 0u, 4u, std::max<uint32_t>(1, 8u * cus), 0u, st);
                 return e; }));
         } else {
             HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] { return survivors(dt2, work); }));
@@ -1287,6 +1344,11 @@ int rasp_destroy(rasp_ctx *c)
         (void)hipStreamSynchronize(c->stream2);
         (void)hipStreamDestroy(c->stream2);
     }
+    if (c->stream3) {
+        (void)hipStreamSynchronize(c->stream3);
+        (void)hipStreamDestroy(c->stream3);
+    }
+    if (c->ev_third) (void)hipEventDestroy(c->ev_third);
     if (c->ev_first) (void)hipEventDestroy(c->ev_first);
     if (c->ev_second) (void)hipEventDestroy(c->ev_second);
     if (c->cstream) (void)hipStreamDestroy(c->cstream);

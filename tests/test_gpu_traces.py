@@ -49,6 +49,10 @@ CASES = {
     "boundaries": (lambda: W.from_programs(1, _boundary_programs(41) * 20, 41, [[3, -4]] * 100, ell=2, s=2),
                    dict(first_pass=1), 9000),
     "uneven": (lambda: W.config3(num_vms=6000, seed=9), dict(lds_words=40, first_pass=576), 20000),
+    # sorted first (n of at most 512), and not
+    "fig1": (lambda: W.fig1(num_vms=2000), dict(first_pass=64, lds_words=152), 30000),
+    "wanderers-n512": (lambda: _wanderers(2000, 512), dict(first_pass=64), 5000),
+    "wanderers-n513": (lambda: _wanderers(2000, 513), dict(first_pass=64), 5000),
     "wanderers": (lambda: _wanderers(700, 1024), dict(first_pass=64), 7000),
     # survivors that go to k_whole without traces: n of one to four lanes a wave,
     # and one word more than it takes; more survivors than its lanes
