@@ -359,7 +359,13 @@ int rasp_free_batch(rasp_ctx *ctx, rasp_batch b);
  *   RASP_OPT_FIRST_PASS    persistent schedule only: transitions every machine
  *                          first runs in a first pass; the machines still
  *                          running then go through the persistent kernel
- *                          (0: persistent kernel only)
+ *                          (0: persistent kernel only).  With memories of at
+ *                          most 1,024 words, 8,192 transitions left and 52
+ *                          bytes a machine free in the arena they are compiled into
+ *                          traces instead; a short list of them runs whole
+ *                          in LDS, and a batch of a few machines a wave does
+ *                          from the start.  Neither under RASP_OPT_GRAPH's replay nor
+ *                          in rasp_run_noalloc is anything compiled
  *   RASP_OPT_FIRST_PASS_KIND  0 (default): the first pass is the plain
  *                          kernel (memory in HBM, one machine per lane); 1: the
  *                          persistent kernel with every machine's memory in
@@ -373,7 +379,8 @@ int rasp_free_batch(rasp_ctx *ctx, rasp_batch b);
  *                          kernel keeps a machine's profiled cells (up to S,
  *                          hashed into S slots) in LDS, every other word in HBM;
  *                          a cell missed later whose slot is empty joins the
- *                          table (replaces RASP_OPT_LDS_WORDS for that launch)
+ *                          table (replaces RASP_OPT_LDS_WORDS for that launch;
+ *                          no effect on a run whose survivors are compiled)
  *   RASP_OPT_PROFILE_STEPS transitions profiled at the end of a hot-cell first
  *                          pass, >= 1 (default 256)
  *   RASP_OPT_MISFIT_WAVES  resident waves per compute unit of the launch that
@@ -409,11 +416,11 @@ int rasp_get_option(rasp_ctx *ctx, int option, int64_t *value);
 enum {
     RASP_KERNEL_PACK = 0,          /* c0 construction                           */
     RASP_KERNEL_PLAIN = 1,         /* one machine per lane step loop            */
-    RASP_KERNEL_PERSISTENT = 2,    /* work-queue step loop                      */
+    RASP_KERNEL_PERSISTENT = 2,    /* step loops over the survivors             */
     RASP_KERNEL_DIGEST = 3,        /* memory digests                            */
     RASP_KERNEL_OTHER = 4,         /* checks, scans, copies, queue reset        */
     RASP_KERNEL_FIRST = 5,         /* work-queue first pass with LDS memory     */
-    RASP_KERNEL_MISFIT = 6,        /* hot-cell misfits' work-queue step loop    */
+    RASP_KERNEL_MISFIT = 6,        /* the part of it on the second stream       */
     RASP_KERNEL_COUNT = 7
 };
 enum { RASP_OPT_PROFILE = 7 };

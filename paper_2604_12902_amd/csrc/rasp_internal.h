@@ -114,7 +114,8 @@ struct TraceArgs {
     uint32_t events, events_sh;        // how often: events general steps and one in 2^events_sh transitions
     uint32_t fulls, fulls_sh;
     uint32_t dense, least;             // machines a wave (0: as few as spread them over the launch), on `least` blocks at least
-    uint32_t few;                      // k_whole: the longest list it takes,
+    uint32_t all;                      // k_whole: this many machines from the first one on, no list (0: list `in`),
+    uint32_t few;                      // the longest list it takes,
     uint32_t spread;                   // the waves it spreads a short one over,
     uint32_t slab;                     // the bytes of LDS of each,
     uint32_t already;                  // and the first pass's transitions

@@ -2452,13 +2452,13 @@ __device__ __forceinline__ uint32_t run_whole(uint32_t base, const gi32 *T, gi32
         // position, and the LDS word of the data (of the next instruction if
         // there is none); returns 0 for a lane it is not common for
         uint32_t ni = 0, np = 0, ad = 0, k = 0;
-        auto decode = [&]() -> uint32_t {
+        auto decode = [&](uint32_t cold, uint32_t used) -> uint32_t {
             k = min(static_cast<uint32_t>(o), 31u);
             const uint32_t ua = static_cast<uint32_t>(a), uj = static_cast<uint32_t>(j);
             // the sign of -a & ~a: a > 0
             const uint32_t test = ISA == 1 ? static_cast<uint32_t>(static_cast<int32_t>((0u - ua) & ~ua) >> 31)
                                            : (a != 0 ? ~0u : 0u);
-            const uint32_t tk = (in(0x20u, k) & test) | (ISA == 1 ? in(0x100u, k) : 0u), us = in(0x1cu, k);
+            const uint32_t tk = (in(0x20u, k) & test) | (ISA == 1 ? in(0x100u, k) : 0u), us = in(used, k);
             const uint32_t i2 = static_cast<uint32_t>(i) + 2u;
             ni = pick(tk, uj, WM ? static_cast<uint32_t>(sext(i2, ws)) : i2);
             uint32_t jm = uj;
@@ -2482,7 +2482,7 @@ __device__ __forceinline__ uint32_t run_whole(uint32_t base, const gi32 *T, gi32
                 ok = min(ok, static_cast<uint32_t>(min(static_cast<int32_t>(ni), top)) ^ static_cast<uint32_t>(top));
             return ok;
         };
-        uint32_t ok = decode();
+        uint32_t ok = decode(cold, 0x1cu);
         // (a counter that is there already: i + 2 may have wrapped)
         if (!POW2 || WM) ok = i > top ? 0u : ok;
         if (!any_lane(min(ok, left) == 0u)) {
@@ -2502,10 +2502,39 @@ __device__ __forceinline__ uint32_t run_whole(uint32_t base, const gi32 *T, gi32
                 o = o2;
                 j = j2;
                 --left;
-                ok = min(decode(), left);
+                ok = min(decode(cold, 0x1cu), left);
             } while (!any_lane(ok == 0u));
         }
         if (left == 0) break;
+        // a READ or an append for some lane, common otherwise (1,024 tiny
+        // machines that print up to 256 words: 103 us with these among the
+        // transitions below, 80 this way)
+        ok = 0;
+        if (any_lane((o == 6) | ((o == 7) & (y0 < r.s)))) {
+            ok = decode(~kCommon & ~(u0 < r.ell ? 0x40u : 0u), 0xdcu);
+            if (n < 2u || ((!POW2 || WM) && i > top)) ok = 0;
+        }
+        if (!any_lane(ok == 0u)) {
+            const uint32_t nx = base + np * kWord;
+            int32_t w = a;
+            if (o == 6) w = T[u0++];
+            lds_i32(pick(in(0x50u, k), ad, spare)) = w;
+            const int32_t o2 = lds_i32(nx), j2 = lds_i32(nx + kWord);
+            const uint32_t d = static_cast<uint32_t>(static_cast<int32_t>(lds_i32(ad)));
+            if (o == 7 && y0 < r.s) Y[y0++] = static_cast<int32_t>(d);
+            const uint32_t ua = static_cast<uint32_t>(a), m3 = in(0x8u, k);
+            uint32_t x;
+            if (ISA == 1) x = ua + (((d ^ m3) - m3) & in(0xcu, k));
+            else x = pick(m3, ua * d, ua + (d & in(0x4u, k)));
+            if (WM) x = static_cast<uint32_t>(sext(x, ws));
+            a = static_cast<int32_t>(pick(in(0x2u, k), static_cast<uint32_t>(j), x));
+            i = static_cast<int32_t>(ni);
+            p = np;
+            o = o2;
+            j = j2;
+            --left;
+            continue;
+        }
         // a transition that is not common for some lane, with general positions
         if (any_lane(stuck<ISA>(static_cast<uint32_t>(o), j, a, i, u0, r.ell))) break;
         const bool taken = ISA == 1 ? (o == 8) | ((o == 5) & (a > 0)) : (o == 5) & (a != 0);
@@ -2537,7 +2566,7 @@ __global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *_
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wib = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave)));
     const uint32_t slab = wib * ta.slab;                 // the wave's LDS
-    const uint64_t total = ta.in == kListFirst ? q->survivors : q->count[ta.in];
+    const uint64_t total = ta.all != 0 ? ta.all : ta.in == kListFirst ? q->survivors : q->count[ta.in];
     if (total > ta.few) return;
     unsigned long long *const head = ta.in == kListFirst ? &q->head : &q->next[ta.in];
     // as few lanes a wave as one wave a SIMD allows, then more lanes, then
@@ -2559,9 +2588,9 @@ __global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *_
         gi32 *M = nullptr, *T = nullptr, *Y = nullptr;
         const DevBatch *bp = nullptr;
         uint64_t v = 0;
-        uint32_t left = 0, limit = 0, ws = 0;
+        uint32_t left = 0, limit = 0, ws = 0, hw = 0;
         if (has) {
-            const uint32_t gid = ta.idx[ta.in][item];
+            const uint32_t gid = ta.all != 0 ? static_cast<uint32_t>(item) : ta.idx[ta.in][item];
             const int k = batch_of(tab, gid);
             bp = &tab->b[k];
             v = gid - tab->start[k];
@@ -2576,10 +2605,14 @@ __global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *_
             const uint32_t budget = tab->budget[k];
             left = limit = ta.left[ta.in] ? ta.left[ta.in][item] : budget > ta.already ? budget - ta.already : 0u;
             has = left != 0 && gany(bp->status)[v] == 0;
+            hw = ta.all != 0 ? min(gany(bp->hw)[v], r.n) : r.n;
         }
         const uint32_t top = wave_max(has ? r.n : 0u);
         for (uint32_t k = 0; k < top; ++k)
-            if (has && k < r.n) dma4((const int32_t *)(M + k), slab / 4u + (k << SH));
+            if (has && k < hw) dma4((const int32_t *)(M + k), slab / 4u + (k << SH));
+        // (c0's zero tail is not stored before a first launch)
+        if (ta.all != 0 && has)
+            for (uint32_t k = hw; k < r.n; ++k) lds_i32(slab + 4u * lane + (k << (SH + 2u))) = 0;
         __builtin_amdgcn_s_waitcnt(0);
         for (uint64_t live; (live = __ballot(has)) != 0;) {
             const uint32_t L = wave_min(has ? left : ~0u);
@@ -2616,6 +2649,10 @@ __global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *_
                 gany(bp->i)[v] = r.i; gany(bp->a)[v] = r.a; gany(bp->u0)[v] = r.u0; gany(bp->y0)[v] = r.y0;
                 gany(bp->steps)[v] += limit - left;
                 if (halted) gany(bp->status)[v] = 1;
+                if (hw < r.n) {
+                    for (uint32_t k = r.n; k < up4(r.n); ++k) M[k] = 0;
+                    gany(bp->hw)[v] = up4(r.n);
+                }
                 has = false;
             }
         }

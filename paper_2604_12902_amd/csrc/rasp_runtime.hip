@@ -25,16 +25,22 @@ constexpr int kTableRing = 16;
 constexpr int kTickets = 4;              // running-count requests in flight per context
 static_assert(sizeof(BatchTable) >= 8 * kMaxMulti * kTickets, "device count slots fit one table slot");
 // fewest transitions left after the first pass for which the survivors are
-// compiled into traces: some 40 us of launches and a few compilations a machine
-// (about 5 us each, in turn with the wave's other lanes) against 0.3 us
-// (memories whole in LDS) or 0.8-1.6 us (HBM) a transition in lockstep.
-// plain-scale with 4,096 left, whole in LDS: 1.9 ms with traces, 1.68 without;
-// 50,021 uneven machines with 16,320 left, in HBM: 5.7 ms against 6.8.
-constexpr uint32_t kTraceMinLeft = 2048, kTraceMinLeftLds = 8192;
-// transitions after which transients are over: traces start there
+// compiled into traces: some 1.5 ms of passes and launches (transients, a few
+// compilations a machine of about 5 us each, in turn with the wave's other
+// lanes, larger tables) and then 0.145 us a transition for the machines that do
+// not run in nodes, against 0.23-0.4 us a transition for all in lockstep.
+// Twelve served requests in epochs of 4,096 transitions: 2.1 ms an epoch with
+// traces, 1.7 without; 50,021 uneven machines with 16,320 left: 5.3 ms against
+// 6.8; plain-scale with 4,032 left: 1.9 against 1.4.
+constexpr uint32_t kTraceMinLeft = 8192;
+// fewest for which transients go first where machines then run whole in LDS
+constexpr uint32_t kWarmMinLeft = 1024;
+// transitions after which transients are over: traces start there, and the
+// lists of k_whole
 constexpr uint32_t kTraceWarm = 512;
 constexpr uint32_t kSortMaxN = 512;       // largest memory for which survivors are sorted first
 constexpr uint32_t kWholeMaxN = 2048;     // largest memory k_whole takes (4 lanes a wave)
+constexpr uint32_t kWholeAll = 8;         // machines a wave with which a batch goes there at once
 constexpr uint32_t kWholeRounds = 2;      // times k_whole's lanes are filled at most
 constexpr uint64_t kLdsGrain = 1280;      // LDS of a block is taken in units of this
 constexpr uint64_t kStageWords = 32ull << 20;    // host-load staging: program + input words per chunk
@@ -920,18 +926,18 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
         wa.few = *few;
         wa.spread = kWholeWpb * static_cast<uint32_t>(c->cus);
         wa.slab = slab;
-        wa.already = cap;
         return launch_whole(tb, isa, pow2, wm, wa, sh, blocks_w, qs, on);
     };
     // a first pass's survivors: whole in LDS if one round takes them all, else
     // the work queue
-    auto survivors = [&](const BatchTable *tb, uint32_t *work) {
+    auto survivors = [&](const BatchTable *tb, uint32_t *list, uint32_t in, uint32_t ran) {
         TraceArgs wa{};
-        wa.idx[kListFirst] = work;
+        wa.idx[in] = list;
+        wa.already = ran;
         uint32_t few;
-        const hipError_t e = whole(tb, wa, kListFirst, 1, &few, st);
-        return e ? e : launch_persistent(tb, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap,
-                                         nullptr, qs, st, kListFirst, nullptr, few);
+        const hipError_t e = whole(tb, wa, in, 1, &few, st);
+        return e ? e : launch_persistent(tb, total, list, ran, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap,
+                                         nullptr, qs, st, in, nullptr, few);
     };
     if (graphed) {
         // replay (capturing on first use) the launch sequence for this key
@@ -957,10 +963,10 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             if (!e && cap > 0 && cap < maxb && lds_first) {
                 e = launch_persistent(gt, total, nullptr, 0, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, cap, work, qs, st);
                 if (!e) e = launch_reset_head(qs, st);
-                if (!e) e = survivors(gt, work);
+                if (!e) e = survivors(gt, work, kListFirst, cap);
             } else if (!e && cap > 0 && cap < maxb) {
                 e = launch_plain(gt, total, cap, isa, pow2, false, wm, work, qs, st);
-                if (!e) e = survivors(gt, work);
+                if (!e) e = survivors(gt, work, kListFirst, cap);
             } else if (!e && cap >= maxb && !lds_first) {
                 e = launch_plain(gt, total, maxb, isa, pow2, false, wm, nullptr, qs, st);
             } else if (!e) {
@@ -981,9 +987,21 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
     }
     // traces: survivors with a budget worth compiling for, in a launch that may allocate
     const bool trace = sched == RASP_SCHED_PERSISTENT && cap > 0 && cap < maxb &&
-                       maxb - cap >= (P >= max_n ? kTraceMinLeftLds : kTraceMinLeft) &&
+                       maxb - cap >= kTraceMinLeft &&
                        max_n <= kTraceMaxN && rs == nullptr && ensure_work(c, total) == RASP_OK && ensure_trace(c, total);
-    if (fused) {
+    // A batch of a few machines a wave runs whole in LDS from the start: the
+    // first pass takes as long for it as for a hundred thousand (64 transitions
+    // in HBM, 42 us of 1,024 machines' 195) and retires no more than the lanes
+    // beside it wait for.
+    const bool direct = sched == RASP_SCHED_PERSISTENT && cap > 0 && cap < maxb && !lds_first && !any_fresh && !trace &&
+                        !hot && rs == nullptr && whole_ok &&
+                        total <= std::min<uint64_t>(kWholeWpb * blocks_w << sh, static_cast<uint64_t>(kWholeAll) * kWholeWpb * c->cus);
+    if (direct) {
+        TraceArgs wa{};
+        wa.all = static_cast<uint32_t>(total);
+        uint32_t few;
+        HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] { return whole(dt, wa, kListFirst, 1, &few, st); }));
+    } else if (fused) {
         // fresh batches present: one persistent launch over every machine
         HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
             return launch_persistent(dt, total, nullptr, 0, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap, nullptr, qs, st); }));
@@ -1145,6 +1163,12 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                     if (!e) e = hipStreamWaitEvent(st, c->ev_third, 0);
                     if (!e) e = general(kListLate, st);
                 } else {
+                    // (one round of k_whole takes as long as the machines
+                    // that do not run in nodes take in the end: uneven 50K,
+                    // 6,234 machines, 2.4 ms instead of 4.9)
+                    uint32_t few;
+                    ta.already = ran;
+                    if (!e) e = whole(dt2, ta, from, 1, &few, st);
                     if (!e) e = traces(from, false, kListGeneral, kListFull, cus, st);
                     if (!e) e = hipEventRecord(c->ev_first, st);
                     if (!e) e = hipStreamWaitEvent(st2, c->ev_first, 0);
@@ -1157,7 +1181,17 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 if (!e) e = queue(kListEnd, 0u, 4u, std::max<uint32_t>(1, 8u * cus), 0u, st);
                 return e; }));
         } else {
-            HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] { return survivors(dt2, work); }));
+            // memories in HBM: transients first, in a pass of their own, after
+            // which the lanes of k_whole may take the rest (50,021 uneven
+            // machines: 14,226 survivors of 64 transitions, 6,234 of 512)
+            const bool warm = rs == nullptr && sched == RASP_SCHED_PERSISTENT && P < max_n && whole_ok && cap < kTraceWarm &&
+                              maxb - cap >= kWarmMinLeft && ensure_trace(c, total);
+            HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
+                if (!warm) return survivors(dt2, work, kListFirst, cap);
+                uint32_t *list = at<uint32_t>(c, c->trace);
+                const hipError_t e = launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
+                                                       kTraceWarm - cap, list, qs, st);
+                return e ? e : survivors(dt2, list, kListWarm, kTraceWarm); }));
         }
         for (uint32_t t = 0; t < k; ++t) bs[t]->dev.fresh = 0;
     } else if (cap >= maxb && !lds_first) {

@@ -36,24 +36,26 @@ def _wanderers(num_vms, n):
 
 
 # budgets on both sides of the fewest transitions traces are compiled for
-# (2,048 after the first pass; 8,192 with memories whole in LDS)
+# (8,192 after the first pass)
 CASES = {
-    "classic-n7": (lambda: _uniform(1, 6000, 1, 7), dict(first_pass=4), 2051),
-    "classic-n1": (lambda: _uniform(2, 3000, 1, 1), dict(first_pass=4), 2052),
-    "classic-n2": (lambda: _uniform(3, 3000, 1, 2), dict(first_pass=4), 2053),
-    "classic-n64": (lambda: _uniform(4, 40000, 1, 64), dict(first_pass=4), 2052),
-    "word-n31": (lambda: _uniform(5, 40000, 0, 31), dict(first_pass=1), 5000),
+    "classic-n7": (lambda: _uniform(1, 6000, 1, 7), dict(first_pass=4), 8195),
+    "classic-n1": (lambda: _uniform(2, 3000, 1, 1), dict(first_pass=4), 8196),
+    "classic-n2": (lambda: _uniform(3, 3000, 1, 2), dict(first_pass=4), 8197),
+    "classic-n64": (lambda: _uniform(4, 40000, 1, 64), dict(first_pass=4), 8196),
+    "word-n31": (lambda: _uniform(5, 40000, 0, 31), dict(first_pass=1), 9000),
     "word-n64-lds64": (lambda: _uniform(6, 20000, 0, 64), dict(first_pass=16, lds_words=64), 8208),
-    "classic-n33-w8": (lambda: _uniform(7, 40000, 1, 33, w=8), dict(first_pass=600), 6000),
-    "word-n40-w29": (lambda: _uniform(8, 20000, 0, 40, w=29), dict(), 4096),
+    "classic-n33-w8": (lambda: _uniform(7, 40000, 1, 33, w=8), dict(first_pass=600), 9000),
+    "word-n40-w29": (lambda: _uniform(8, 20000, 0, 40, w=29), dict(), 8300),
     "boundaries": (lambda: W.from_programs(1, _boundary_programs(41) * 20, 41, [[3, -4]] * 100, ell=2, s=2),
                    dict(first_pass=1), 9000),
     "uneven": (lambda: W.config3(num_vms=6000, seed=9), dict(lds_words=40, first_pass=576), 20000),
+    # more survivors than one round of k_whole's lanes
+    "uneven-many": (lambda: W.config3(num_vms=90000, seed=33), dict(first_pass=64), 8400),
     # sorted first (n of at most 512), and not
     "fig1": (lambda: W.fig1(num_vms=2000), dict(first_pass=64, lds_words=152), 30000),
-    "wanderers-n512": (lambda: _wanderers(2000, 512), dict(first_pass=64), 5000),
-    "wanderers-n513": (lambda: _wanderers(2000, 513), dict(first_pass=64), 5000),
-    "wanderers": (lambda: _wanderers(700, 1024), dict(first_pass=64), 7000),
+    "wanderers-n512": (lambda: _wanderers(2000, 512), dict(first_pass=64), 8300),
+    "wanderers-n513": (lambda: _wanderers(2000, 513), dict(first_pass=64), 8300),
+    "wanderers": (lambda: _wanderers(700, 1024), dict(first_pass=64), 9000),
     # survivors that go to k_whole without traces: n of one to four lanes a wave,
     # and one word more than it takes; more survivors than its lanes
     "whole-n2048": (lambda: _wanderers(300, 2048), dict(first_pass=64), 4000),
@@ -61,8 +63,20 @@ CASES = {
     "whole-n1": (lambda: _uniform(12, 1025, 1, 1), dict(first_pass=1), 700),
     "whole-n250-w16": (lambda: _uniform(13, 30000, 0, 250, w=16), dict(first_pass=8, lds_words=252), 4000),
     "whole-n1024-many": (lambda: _wanderers(9000, 1024), dict(first_pass=64), 1000),
+    # transients in a pass of their own (memories in HBM, 1,024 transitions
+    # left), with survivors for k_whole and for the work queue, and without
+    "warm-whole": (lambda: W.config3(num_vms=9000, seed=30), dict(lds_words=0, first_pass=64), 1088),
+    "warm-queue": (lambda: W.config3(num_vms=70000, seed=31), dict(first_pass=3), 2000),
+    "no-warm": (lambda: W.config3(num_vms=9000, seed=32), dict(lds_words=0, first_pass=64), 1087),
+    # whole in LDS from the start, c0's zero tails not stored yet: up to 8
+    # machines a wave (8,192 on 256 CUs), and one more
+    "direct-n3": (lambda: _uniform(15, 1000, 1, 3), dict(first_pass=4), 40),
+    "direct-n63": (lambda: _uniform(16, 8192, 1, 63), dict(first_pass=4), 900),
+    "first-n63": (lambda: _uniform(16, 8193, 1, 63), dict(first_pass=4), 900),
+    "direct-word-n129-w8": (lambda: _uniform(17, 3000, 0, 127, w=8), dict(), 1500),
+    "direct-n1023": (lambda: _wanderers(4097, 1023), dict(), 1000),
     # more of them than k_whole takes: the work queue steps them
-    "wanderers-many": (lambda: _wanderers(40000, 1024), dict(first_pass=64), 3500),
+    "wanderers-many": (lambda: _wanderers(40000, 1024), dict(first_pass=64), 8300),
 }
 
 
@@ -99,24 +113,24 @@ def test_traces_bit_exact(R, case):
         st = _random_states(b, seed=51 + isa)
         with _context(R, dict(first_pass=2)) as c:
             h = c.load_state(b, dict(i=st.i, a=st.a, u0=st.u0, y0=st.y0, steps=st.steps, y=st.Y, mem=st.mem))
-            c.run(h, 3000)
-            oracle.advance(st, 3000)
+            c.run(h, 8200)
+            oracle.advance(st, 8200)
             compare(c.fetch(h, mem=True), st)
     elif case == "runs":
         # one run's machines go on in the next
         b = W.config3(num_vms=3000, seed=10)
         with _context(R, dict(first_pass=100)) as c:
             h = c.load(b)
-            for budget in (2500, 1, 2148, 4000):
+            for budget in (8500, 1, 8292, 4000):
                 c.run(h, budget)
-            compare(c.fetch(h, mem=True), oracle.run(b, 8649, threads=8))
+            compare(c.fetch(h, mem=True), oracle.run(b, 20793, threads=8))
     elif case == "multi":
         # several batches in one launch: the lists hold machines of all
         bs = [W.config3(num_vms=1000 + 77 * k, seed=20 + k) for k in range(3)]
         with _context(R, dict(first_pass=64)) as c:
             hs = [c.load(b) for b in bs]
-            c.run_multi(hs, [6000, 2600, 6000])
-            for h, b, budget in zip(hs, bs, (6000, 2600, 6000)):
+            c.run_multi(hs, [9000, 2600, 9000])
+            for h, b, budget in zip(hs, bs, (9000, 2600, 9000)):
                 compare(c.fetch(h, mem=True), oracle.run(b, budget, threads=8))
     elif case in ("graph", "noalloc"):
         # the survivors' launches captured, and without an allocation
@@ -137,8 +151,8 @@ def test_traces_bit_exact(R, case):
         room = R.rasp_batch_footprint(R.make_desc(b)) + 34 * b.N + (1 << 20)
         with _context(R, dict(first_pass=4), room) as c:
             h = c.load(b)
-            c.run(h, 2100)
-            compare(c.fetch(h), oracle.run(b, 2100, threads=8), mem=False)
+            c.run(h, 8200)
+            compare(c.fetch(h), oracle.run(b, 8200, threads=8), mem=False)
 
 
 # a load's waves walk 4 to 64 machines each, by the machines there are
