@@ -147,7 +147,26 @@ constexpr uint32_t kTraceNodes2 = 48, kTraceData2 = 40;      // 2 waves a CU
 // n = 2,048: 159 ms with traces, 144 without).
 constexpr uint32_t kTraceMaxN = 1u << 10;
 constexpr uint32_t trace_lds_bytes(uint32_t NO, uint32_t ND) { return NO * (1024u + 128u) + (ND + 2u) * 256u + ND * 128u; }
-constexpr uint32_t whole_lds_bytes(uint32_t max_n, uint32_t sh) { return (max_n + 2u) << (sh + 2u); }
+constexpr uint32_t kWholeMaxN = 2048;  // largest memory k_whole takes (4 lanes a wave)
+constexpr uint64_t kLdsGrain = 1280;   // LDS of a block is taken in units of this
+constexpr uint64_t whole_lds_bytes(uint32_t max_n, uint32_t sh) { return (max_n + 2ull) << (sh + 2u); }
+// A launch of k_whole: 2^sh lanes a wave, each wave with `slab` bytes of LDS,
+// on `blocks` blocks; no blocks where the memories are too large for it.
+struct WholeShape {
+    uint32_t sh, slab, blocks;
+};
+constexpr WholeShape whole_shape(uint32_t max_n, uint64_t total, uint64_t lds, uint32_t cus)
+{
+    WholeShape w{6, 0, 0};
+    if (max_n > kWholeMaxN) return w;
+    while (w.sh > 2 && kWholeWpb * whole_lds_bytes(max_n, w.sh) > lds) --w.sh;
+    const uint64_t slab = whole_lds_bytes(max_n, w.sh);
+    const uint64_t block = (kWholeWpb * slab + kLdsGrain - 1) / kLdsGrain * kLdsGrain;
+    const uint64_t per_cu = lds / block < 8 ? lds / block : 8, most = (total + kWholeWpb - 1) / kWholeWpb;
+    w.slab = static_cast<uint32_t>(slab);
+    w.blocks = static_cast<uint32_t>(most < per_cu * cus ? most : per_cu * cus);
+    return w;
+}
 
 // Descriptor-check error bits.
 enum : uint32_t {

@@ -39,10 +39,8 @@ constexpr uint32_t kWarmMinLeft = 1024;
 // lists of k_whole
 constexpr uint32_t kTraceWarm = 512;
 constexpr uint32_t kSortMaxN = 512;       // largest memory for which survivors are sorted first
-constexpr uint32_t kWholeMaxN = 2048;     // largest memory k_whole takes (4 lanes a wave)
 constexpr uint32_t kWholeAll = 8;         // machines a wave with which a batch goes there at once
 constexpr uint32_t kWholeRounds = 2;      // times k_whole's lanes are filled at most
-constexpr uint64_t kLdsGrain = 1280;      // LDS of a block is taken in units of this
 constexpr uint64_t kStageWords = 32ull << 20;    // host-load staging: program + input words per chunk
 constexpr uint64_t kStageVms = 1ull << 20;       // and machines per chunk
 
@@ -912,13 +910,9 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
     // the machines of a list whole in LDS, one wave a SIMD, if they fill its
     // lanes at most `rounds` times; `few`: the longest such list, which the work
     // queue's launch then leaves alone (0: every list is the queue's)
-    uint32_t sh = 6;
-    while (sh > 2 && kWholeWpb * whole_lds_bytes(max_n, sh) > lds) --sh;
-    const uint32_t slab = whole_lds_bytes(max_n, sh);
-    const uint32_t blocks_w = static_cast<uint32_t>(std::min<uint64_t>(
-        (total + kWholeWpb - 1) / kWholeWpb,
-        std::min<uint64_t>(8, lds / align_up(kWholeWpb * slab, kLdsGrain)) * static_cast<uint64_t>(c->cus)));
-    const bool whole_ok = max_n <= kWholeMaxN;
+    const WholeShape ws = whole_shape(max_n, total, lds, static_cast<uint32_t>(c->cus));
+    const uint32_t sh = ws.sh, slab = ws.slab, blocks_w = ws.blocks;
+    const bool whole_ok = blocks_w != 0;
     auto whole = [&](const BatchTable *tb, TraceArgs wa, uint32_t in, uint32_t rounds, uint32_t *few, hipStream_t on) {
         *few = whole_ok ? rounds * (kWholeWpb * blocks_w << sh) : 0;
         if (!whole_ok) return hipSuccess;

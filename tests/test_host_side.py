@@ -1,0 +1,54 @@
+"""librasp's host-side headers, compiled for the CPU against a model of the HIP
+runtime (tests/hip_model)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _run(tmp_path, main):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    src, exe = tmp_path / "main.cpp", tmp_path / "main"
+    src.write_text(main)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-g", "-pthread", "-I" + os.path.join(ROOT, "tests", "hip_model"),
+                    "-I" + os.path.join(ROOT, "paper_2604_12902_amd", "csrc"), "-o", str(exe), str(src)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stdout[-2000:], r.stderr[-2000:])
+
+
+def test_whole_shape_of_every_memory_size(tmp_path):
+    """k_whole's launch over all sizes a load accepts (1 to 2^30 words), those
+    whose bytes of a wave's slots are a multiple of 2^32 among them: blocks that
+    fit a compute unit's LDS, or none."""
+    _run(tmp_path, r"""
+#include "rasp_internal.h"
+#include <cstdio>
+#include <initializer_list>
+#include <cstdlib>
+using namespace rasp;
+static void check(uint32_t n, uint64_t total, uint64_t lds, uint32_t cus)
+{
+    const WholeShape w = whole_shape(n, total, lds, cus);
+    bool ok = n > kWholeMaxN ? w.blocks == 0 : w.slab == whole_lds_bytes(n, w.sh) && w.sh >= 2 && w.sh <= 6;
+    if (w.blocks) ok = ok && uint64_t(kWholeWpb) * w.slab <= lds && w.blocks <= 8 * cus && (w.blocks - 1) * uint64_t(kWholeWpb) < total;
+    if (n <= kWholeMaxN && lds == 160 * 1024) ok = ok && w.blocks;
+    if (!ok) { std::printf("n %u total %llu lds %llu cus %u: sh %u slab %u blocks %u\n", n, (unsigned long long)total,
+                           (unsigned long long)lds, cus, w.sh, w.slab, w.blocks); std::exit(1); }
+}
+int main()
+{
+    for (uint64_t lds : {64ull * 1024, 160ull * 1024})
+        for (uint32_t cus : {1u, 32u, 256u})
+            for (uint64_t total : {1ull, 5ull, 100003ull, (1ull << 32) - 1}) {
+                for (uint32_t n = 1; n <= 4096; ++n) check(n, total, lds, cus);
+                for (uint32_t k = 12; k <= 30; ++k)
+                    for (uint32_t m = 1; (uint64_t(m) << k) <= kMaxMemWords && m <= 3; ++m)
+                        for (int d = -3; d <= 0; ++d) check((m << k) + d, total, lds, cus);
+            }
+}
+""")
