@@ -35,19 +35,27 @@ public:
 
     ~HostCopy() { close(); }
 
-    // Start of a call that uses put() or get(): the stream has been waited for
-    // since the last one.
-    void begin()
+    // Start of a call that uses put() or get().  The area starts anew, so a call
+    // that ended without settled() or flush() (an error between its copies) is
+    // waited for here: its copies may still read or write the area.
+    hipError_t begin()
+    {
+        const hipError_t e = used_ != 0 ? hipStreamSynchronize(on_) : hipSuccess;
+        settled();
+        return e;
+    }
+
+    // The stream has been waited for since the last copy.
+    void settled()
     {
         used_ = 0;
         got_.clear();
     }
 
-    // A copy to the device whose source may be reused on return.  The caller
-    // waits for the stream before the next begin().
+    // A copy to the device whose source may be reused on return.
     hipError_t put(int device, void *dst, const void *src, uint64_t bytes, hipStream_t st)
     {
-        char *p = take(device, bytes);
+        char *p = take(device, bytes, st);
         if (!p) return copy(device, dst, src, bytes, hipMemcpyHostToDevice, st);
         std::memcpy(p, src, bytes);
         return hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, st);
@@ -56,7 +64,7 @@ public:
     // A copy from the device whose data is there after flush().
     hipError_t get(int device, void *dst, const void *src, uint64_t bytes, hipStream_t st)
     {
-        char *p = take(device, bytes);
+        char *p = take(device, bytes, st);
         if (!p) return copy(device, dst, src, bytes, hipMemcpyDeviceToHost, st);
         const hipError_t e = hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToHost, st);
         if (!e) got_.push_back({dst, p, bytes});
@@ -69,7 +77,7 @@ public:
         const hipError_t e = hipStreamSynchronize(st);
         if (!e)
             for (const Got &g : got_) std::memcpy(g.dst, g.p, g.bytes);
-        begin();
+        settled();
         return e;
     }
 
@@ -137,12 +145,13 @@ private:
     };
 
     // `bytes` of the area, or null
-    char *take(int device, uint64_t bytes)
+    char *take(int device, uint64_t bytes, hipStream_t st)
     {
         const uint64_t n = (bytes + 255) & ~255ull;
         if (bytes == 0 || bytes > kSmall || used_ + n > kArea || !open(device) || got_.size() == got_.capacity()) return nullptr;
         char *p = base_ + kWorkers * kSlots * kChunk + used_;
         used_ += n;
+        on_ = st;
         return p;
     }
 
@@ -259,7 +268,8 @@ private:
     char *base_ = nullptr;
     bool failed_ = false;                // opened once already (base_ null: without success)
     Slot slots_[kWorkers][kSlots];
-    uint64_t used_ = 0;                  // of the area
+    uint64_t used_ = 0;                  // of the area, by copies on the stream
+    hipStream_t on_ = nullptr;
     std::vector<Got> got_;
     std::vector<std::thread> helpers_;
     std::mutex mu_;

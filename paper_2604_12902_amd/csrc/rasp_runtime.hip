@@ -473,12 +473,11 @@ int load_common(rasp_ctx *c, const rasp_batch_desc *d, std::unique_ptr<Batch> &o
             return bail(RASP_E_NOMEM);
         }
         carve_words(at<char>(c, B->words), B->sum_n_pad, B->sum_ell, &B->dev);
-        // (the stream is waited for after every chunk of machines below)
-        c->host.begin();
         auto H2D = [&](void *dst, const void *src, uint64_t bytes) {
             return c->host.put(c->device, dst, src, bytes, st);
         };
-        hipError_t e = hipSuccess;
+        // (the stream is waited for after every chunk of machines below)
+        hipError_t e = c->host.begin();
         if (!e) e = H2D(B->dev.n, h.n.data(), 4 * N);
         if (!e) e = H2D(B->dev.ell, h.ell.data(), 4 * N);
         if (!e) e = H2D(B->dev.s, h.s.data(), 4 * N);
@@ -542,7 +541,7 @@ int load_common(rasp_ctx *c, const rasp_batch_desc *d, std::unique_ptr<Batch> &o
             if (!e) e = timed_launch(c, RASP_KERNEL_PACK, [&] { return launch_pack(view, pg, po, pg, to, st); });
             // the staging buffer and the host offset vectors are reused: wait
             if (!e) e = hipStreamSynchronize(st);
-            c->host.begin();
+            if (!e) c->host.settled();
             B->tails = true;
             v0 = v1;
         }
@@ -1455,13 +1454,13 @@ int rasp_load_state(rasp_ctx *c, const rasp_batch_desc *d, const rasp_outputs *s
         arena_free(c, &b.meta);
         return code;
     };
-    // (the stream is waited for before the call returns)
-    c->host.begin();
     auto up = [&](void *dst, const void *src, uint64_t bytes) {
         return kind == hipMemcpyHostToDevice ? c->host.put(c->device, dst, src, bytes, st)
                                              : hipMemcpyAsync(dst, src, bytes, kind, st);
     };
-    hipError_t e = up(b.dev.i, s->i, 4 * N);
+    // (the stream is waited for before the call returns)
+    hipError_t e = c->host.begin();
+    if (!e) e = up(b.dev.i, s->i, 4 * N);
     if (!e) e = up(b.dev.a, s->a, 4 * N);
     if (!e) e = up(b.dev.u0, s->u0, 4 * N);
     if (!e) e = up(b.dev.y0, s->y0, 4 * N);
@@ -1496,6 +1495,7 @@ int rasp_load_state(rasp_ctx *c, const rasp_batch_desc *d, const rasp_outputs *s
     if (!e) b.status_stale = false;
     if (!e) e = hipMemcpyAsync(errw, derr, 4, hipMemcpyDeviceToHost, st);
     if (!e) e = hipStreamSynchronize(st);
+    if (!e) c->host.settled();
     if (e) { fail(c, RASP_E_DEVICE, "state load: %s", hipGetErrorString(e)); return undo(RASP_E_DEVICE); }
     if (*errw & kErrStateRange) { fail(c, RASP_E_INVAL, "state has u0 > l or y0 > s"); return undo(RASP_E_INVAL); }
     if (*errw) { fail(c, RASP_E_INVAL, "a word of the state is not a %u-bit value", b.wbits); return undo(RASP_E_INVAL); }
@@ -1647,8 +1647,22 @@ int rasp_fetch_outputs(rasp_ctx *c, rasp_batch h, const rasp_outputs *o)
         return async || k != hipMemcpyDeviceToHost ? hipMemcpyAsync(dst, src, bytes, k, on)
                                                    : c->host.get(c->device, dst, src, bytes, on);
     };
-    if (!async) c->host.begin();
-    Alloc digests;
+    // whichever way a fetch that waits ends, none of its copies is in flight
+    // behind it and its scratch is back in the arena
+    Alloc digests, tmp;
+    struct Settle {
+        rasp_ctx *c;
+        hipStream_t st;
+        Alloc *a, *b;
+        ~Settle()
+        {
+            if (!c) return;
+            (void)c->host.flush(st);
+            arena_free(c, a);
+            arena_free(c, b);
+        }
+    } settle{async ? nullptr : c, st, &digests, &tmp};
+    if (!async) HIPCHK(c, c->host.begin());
     if (kind == hipMemcpyDeviceToDevice) {
         if (o->status || o->steps || o->i || o->a || o->u0 || o->y0)
             HIPCHK(c, timed_launch(c, RASP_KERNEL_OTHER, [&] {
@@ -1662,7 +1676,6 @@ int rasp_fetch_outputs(rasp_ctx *c, rasp_batch h, const rasp_outputs *o)
         if (o->y0) HIPCHK(c, copy(o->y0, b->dev.y0, 4 * N, kind, st));
     }
     if (o->y && b->sum_s) HIPCHK(c, copy(o->y, b->dev.Y, 4 * b->sum_s, kind, st));
-    Alloc tmp;
     if (o->mem_digest) {
         if (kind == hipMemcpyDeviceToDevice) {
             HIPCHK(c, timed_launch(c, RASP_KERNEL_DIGEST, [&] { return launch_digest(b->dev, o->mem_digest, st); }, st));
@@ -1714,6 +1727,7 @@ int rasp_fetch_outputs(rasp_ctx *c, rasp_batch h, const rasp_outputs *o)
         return RASP_OK;
     }
     HIPCHK(c, c->host.flush(st));
+    settle.c = nullptr;
     arena_free(c, &digests);
     return RASP_OK;
 }

@@ -1,4 +1,5 @@
 """GPU parity where a launch's sizes or the arena come to their limits."""
+import numpy as np
 import pytest
 
 import oracle
@@ -29,3 +30,29 @@ def test_memories_far_beyond_a_slot(R, n, graph):
         h = c.load(b)
         c.run(h, 200)
         compare(c.fetch(h, mem=True), oracle.run(b, 200))
+
+
+# an arena with room for a batch but not for a dump of its memories: the fetch
+# behind a run fails, and the batch loaded next is whole
+@pytest.mark.parametrize("num_vms", [1500, 20000])
+def test_load_after_a_fetch_without_room(R, num_vms):
+    print("case: fetch without room", num_vms, flush=True)
+    first = W.config3(num_vms=num_vms, seed=61)
+    first.mem_words = np.full(num_vms, 1025, np.uint32)
+    then = W.config3(num_vms=num_vms, seed=62)
+    then.mem_words = np.full(num_vms, 1025, np.uint32)
+    room = max(R.rasp_batch_footprint(R.make_desc(b)) for b in (first, then)) + 100 * num_vms + (1 << 20)
+    room += 4 * max(first.prog.size + first.tape.size, then.prog.size + then.tape.size)
+    with _context(R, dict(first_pass=64), room) as c:
+        h = c.load(first)
+        c.run(h, 30000)
+        with pytest.raises(R.RaspError) as e:
+            c.fetch(h, mem=True)
+        assert e.value.code == R.RASP_E_NOMEM
+        c.free(h)
+        h = c.load(then)
+        c.run(h, 3000)
+        got = c.fetch(h, digest=True)
+        want = oracle.run(then, 3000, threads=8)
+        compare(got, want, mem=False)
+        assert np.array_equal(got["mem_digest"], oracle.digest(want))

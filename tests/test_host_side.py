@@ -52,3 +52,46 @@ int main()
             }
 }
 """)
+
+
+HOSTCOPY = r"""
+#include "rasp_hostcopy.h"
+#include <cstdio>
+#include <cstdlib>
+using namespace rasp;
+typedef std::vector<char> Bytes;
+static Bytes noise(size_t n, unsigned seed)
+{
+    Bytes b(n);
+    for (auto &c : b) c = char((seed = seed * 1664525u + 1013904223u) >> 24);
+    return b;
+}
+static void expect(bool ok, const char *what) { if (!ok) { std::printf("%s\n", what); std::exit(1); } }
+"""
+
+
+def test_copies_of_a_call_that_failed_do_not_land_in_the_next_ones(tmp_path):
+    """A fetch that gives up between its copies (no room for the next one), then
+    a load: the fetch's copies, still in flight, may not land in the pinned area
+    once the load has put its own bytes there."""
+    _run(tmp_path, HOSTCOPY + r"""
+int main()
+{
+    HostCopy h;
+    Stream s;
+    for (size_t n : {100u, 4096u, 262144u}) {
+        const Bytes old = noise(n, 1), fresh = noise(n, 2);
+        Bytes out(n), dev(n);
+        h.begin();
+        expect(h.get(0, out.data(), old.data(), n, &s) == hipSuccess, "get");
+        h.begin();                       // the next call: the fetch never waited
+        expect(h.put(0, dev.data(), fresh.data(), n, &s) == hipSuccess, "put");
+        expect(hipStreamSynchronize(&s) == hipSuccess, "wait");
+        expect(dev == fresh, "the load's bytes were overwritten");
+        expect(h.flush(&s) == hipSuccess, "flush");
+        // and one that waits delivers what it got
+        h.begin();
+        expect(h.get(0, out.data(), old.data(), n, &s) == hipSuccess && h.flush(&s) == hipSuccess && out == old, "fetch");
+    }
+}
+""")
