@@ -1,22 +1,27 @@
 // Copies between ordinary (pageable) host memory and the device, through a
-// context's own pinned chunks on a few threads.
+// context's own pinned memory.
 //
 // hipMemcpyAsync on pageable memory moves it through the runtime's staging
-// buffer on the calling thread: 10 GB/s into memory the caller has just
-// allocated (its pages are touched first by the copy), 25 GB/s out of memory
-// in use.  Here kWorkers threads (the caller and its helpers) claim chunks in
-// turn; each keeps two pinned chunks, so its own copy in host memory overlaps
-// the device's, and the pages are touched by all of them.
+// buffer on the calling thread, and waits.  That is 30 GB/s up and 17 down, but
+// 4 down into memory the caller has just allocated, whose pages the copy
+// touches first.  Large copies down go in chunks: kWorkers threads (the caller
+// and its helpers) claim them in turn; each keeps two pinned chunks, so its own
+// copy in host memory overlaps the device's, and the pages are touched by all
+// of them.  Small copies (at most 256 KiB) of one call go through one pinned
+// area, without a wait for each.
 #ifndef RASP_HOSTCOPY_H
 #define RASP_HOSTCOPY_H
 
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <cstdint>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -27,9 +32,15 @@ class HostCopy {
 public:
     static constexpr uint32_t kWorkers = 4, kSlots = 2;
     static constexpr uint64_t kChunk = 1ull << 20, kChunkMin = 256ull << 10;
-    // Smallest copy that goes through the chunks: a helper wakes in some 30 us,
-    // which is what 512 KiB take on one thread.
-    static constexpr uint64_t kMin = 512ull << 10;
+    // Smallest copies that go in chunks (a helper wakes in some 30 us), plain
+    // against chunks: down into new pages 1 MiB 241 us against 207, 4 MiB 982
+    // against 518; into pages that are there 3 MiB 183 against 224, 4 MiB 242
+    // against 245, 8 MiB 476 against 340; up 16 MiB 459 against 575, 64 MiB 2258
+    // against 2152.
+    static constexpr uint64_t kMinNew = 1ull << 20, kMinDown = 4ull << 20, kMinUp = 64ull << 20;
+    // Chunks and helpers take some 1 ms to make, which is what they gain over
+    // 8 MiB: they are made once copies of that size have been.
+    static constexpr uint64_t kOpenAfter = 8ull << 20;
     // the pinned area of small copies, and the largest of them
     static constexpr uint64_t kArea = 1ull << 20, kSmall = 256ull << 10;
 
@@ -55,7 +66,7 @@ public:
     // A copy to the device whose source may be reused on return.
     hipError_t put(int device, void *dst, const void *src, uint64_t bytes, hipStream_t st)
     {
-        char *p = take(device, bytes, st);
+        char *p = take(bytes, st);
         if (!p) return copy(device, dst, src, bytes, hipMemcpyHostToDevice, st);
         std::memcpy(p, src, bytes);
         return hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, st);
@@ -64,7 +75,7 @@ public:
     // A copy from the device whose data is there after flush().
     hipError_t get(int device, void *dst, const void *src, uint64_t bytes, hipStream_t st)
     {
-        char *p = take(device, bytes, st);
+        char *p = take(bytes, st);
         if (!p) return copy(device, dst, src, bytes, hipMemcpyDeviceToHost, st);
         const hipError_t e = hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToHost, st);
         if (!e) got_.push_back({dst, p, bytes});
@@ -88,7 +99,8 @@ public:
     {
         if (bytes == 0) return hipSuccess;
         const bool up = kind == hipMemcpyHostToDevice;
-        if (bytes < kMin || !(up || kind == hipMemcpyDeviceToHost) || pinned(up ? src : dst) || !open(device))
+        if (bytes < kMinNew || !(up || kind == hipMemcpyDeviceToHost) ||
+            bytes < (up ? kMinUp : present(dst, bytes) ? kMinDown : kMinNew) || pinned(up ? src : dst) || !open(device, bytes))
             return hipMemcpyAsync(dst, src, bytes, kind, st);
         const uint64_t chunk = std::min<uint64_t>(kChunk, std::max<uint64_t>(kChunkMin, (bytes / (kWorkers * kSlots) + 4095) & ~4095ull));
         {
@@ -120,16 +132,9 @@ public:
         wake_.notify_all();
         for (auto &t : helpers_) t.join();
         helpers_.clear();
-        if (base_) {
-            for (auto &w : slots_)
-                for (auto &s : w) {
-                    if (s.busy) (void)hipEventSynchronize(s.ev);
-                    if (s.ev) (void)hipEventDestroy(s.ev);
-                    s = Slot{};
-                }
-            (void)hipHostFree(base_);
-            base_ = nullptr;
-        }
+        close_chunks();
+        if (area_) (void)hipHostFree(area_);
+        area_ = nullptr;
     }
 
 private:
@@ -144,15 +149,50 @@ private:
         bool busy = false;               // a copy to the device still reads it
     };
 
-    // `bytes` of the area, or null
-    char *take(int device, uint64_t bytes, hipStream_t st)
+    void close_chunks()
+    {
+        if (!chunks_) return;
+        for (auto &w : slots_)
+            for (auto &s : w) {
+                if (s.busy) (void)hipEventSynchronize(s.ev);
+                if (s.ev) (void)hipEventDestroy(s.ev);
+                s = Slot{};
+            }
+        (void)hipHostFree(chunks_);
+        chunks_ = nullptr;
+    }
+
+    // `bytes` of the area, or null; the area is made at the first small copy
+    char *take(uint64_t bytes, hipStream_t st)
     {
         const uint64_t n = (bytes + 255) & ~255ull;
-        if (bytes == 0 || bytes > kSmall || used_ + n > kArea || !open(device) || got_.size() == got_.capacity()) return nullptr;
-        char *p = base_ + kWorkers * kSlots * kChunk + used_;
+        if (bytes == 0 || bytes > kSmall || used_ + n > kArea || (!area_ && !open_area()) || got_.size() == got_.capacity())
+            return nullptr;
+        char *p = area_ + used_;
         used_ += n;
         on_ = st;
         return p;
+    }
+
+    bool open_area()
+    {
+        if (no_area_) return false;
+        no_area_ = true;
+        try {
+            got_.reserve(16);
+        } catch (...) {
+            return false;
+        }
+        area_ = host_malloc(kArea);
+        return area_ != nullptr;
+    }
+
+    static char *host_malloc(uint64_t bytes)
+    {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess) return static_cast<char *>(p);
+        (void)hipGetLastError();
+        return nullptr;
     }
 
     static bool pinned(const void *p)
@@ -166,30 +206,38 @@ private:
         return a.type != hipMemoryTypeUnregistered;
     }
 
-    // the chunks and the helpers, made at the first copy that wants them
-    bool open(int device)
+    // are the pages of this memory there already (by its first, middle and last)
+    static bool present(const void *p, uint64_t bytes)
     {
-        if (base_) return true;
+        const uint64_t page = static_cast<uint64_t>(sysconf(_SC_PAGESIZE)), a = reinterpret_cast<uint64_t>(p);
+        for (uint64_t at : {a, a + bytes / 2, a + bytes - 1}) {
+            unsigned char in = 1;
+            if (mincore(reinterpret_cast<void *>(at / page * page), 1, &in) == 0 && !(in & 1)) return false;
+        }
+        return true;
+    }
+
+    // the chunks and the helpers
+    bool open(int device, uint64_t bytes)
+    {
+        if (chunks_) return true;
         if (failed_) return false;
+        wanted_ += bytes;
+        if (wanted_ < kOpenAfter) return false;
         failed_ = true;
         device_ = device;
-        if (hipHostMalloc(reinterpret_cast<void **>(&base_), kWorkers * kSlots * kChunk + kArea, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            base_ = nullptr;
-            return false;
-        }
+        if (!(chunks_ = host_malloc(kWorkers * kSlots * kChunk))) return false;
         for (uint32_t w = 0; w < kWorkers; ++w)
             for (uint32_t s = 0; s < kSlots; ++s) {
-                slots_[w][s].p = base_ + (w * kSlots + s) * kChunk;
+                slots_[w][s].p = chunks_ + (w * kSlots + s) * kChunk;
                 if (hipEventCreateWithFlags(&slots_[w][s].ev, hipEventDisableTiming) != hipSuccess) {
                     (void)hipGetLastError();
                     slots_[w][s].ev = nullptr;
-                    close();
+                    close_chunks();
                     return false;
                 }
             }
         try {
-            got_.reserve(16);
             helpers_.reserve(kWorkers);
             for (uint32_t w = 1; w < kWorkers; ++w) helpers_.emplace_back([this, w] { help(w); });
         } catch (...) {
@@ -265,8 +313,9 @@ private:
     }
 
     int device_ = 0;
-    char *base_ = nullptr;
-    bool failed_ = false;                // opened once already (base_ null: without success)
+    char *chunks_ = nullptr, *area_ = nullptr;
+    uint64_t wanted_ = 0;                // bytes that would have gone in chunks so far
+    bool failed_ = false, no_area_ = false;      // tried already (null: without success)
     Slot slots_[kWorkers][kSlots];
     uint64_t used_ = 0;                  // of the area, by copies on the stream
     hipStream_t on_ = nullptr;

@@ -95,3 +95,78 @@ int main()
     }
 }
 """)
+
+
+def test_small_copies_open_no_more_than_the_area(tmp_path):
+    """Copies up to 256 KiB need the 1 MiB area and nothing else, larger ones
+    the chunks, events and helpers only from the sizes and the sum that pay for
+    them; every way moves the right bytes, and all of it is given back."""
+    _run(tmp_path, HOSTCOPY + r"""
+#include <dirent.h>
+static int threads()
+{
+    int n = 0;
+    DIR *d = opendir("/proc/self/task");
+    while (dirent *e = readdir(d)) n += e->d_name[0] != '.';
+    closedir(d);
+    return n;
+}
+int main()
+{
+    Stream s;
+    const size_t most = 64 << 20;
+    const Bytes src = noise(most, 3);
+    Bytes dev(most), warm(most);
+    auto up = [&](HostCopy &h, size_t n) {
+        std::fill(dev.begin(), dev.begin() + n, 0);
+        expect(h.begin() == hipSuccess && h.put(0, dev.data(), src.data(), n, &s) == hipSuccess &&
+               hipStreamSynchronize(&s) == hipSuccess && std::equal(src.begin(), src.begin() + n, dev.begin()), "up");
+        h.settled();
+    };
+    auto down = [&](HostCopy &h, char *out, size_t n) {
+        expect(h.begin() == hipSuccess && h.get(0, out, dev.data(), n, &s) == hipSuccess && h.flush(&s) == hipSuccess &&
+               std::equal(out, out + n, dev.begin()), "down");
+    };
+    auto down_new = [&](HostCopy &h, size_t n) {
+        char *p = static_cast<char *>(mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0));
+        down(h, p, n);
+        munmap(p, n);
+    };
+    auto opened = [&](bool area, bool chunks) {
+        expect(model().pinned_bytes == (area ? HostCopy::kArea : 0) + (chunks ? HostCopy::kWorkers * HostCopy::kSlots * HostCopy::kChunk : 0) &&
+               model().events == (chunks ? int(HostCopy::kWorkers * HostCopy::kSlots) : 0) &&
+               threads() == (chunks ? int(HostCopy::kWorkers) : 1), "opened");
+    };
+    {
+        HostCopy h;
+        for (size_t n : {1u, 300u, 262144u, 262145u, 1048575u}) {
+            up(h, n);
+            down(h, warm.data(), n);
+            down_new(h, n);
+            opened(true, false);
+        }
+    }
+    opened(false, false);
+    {
+        HostCopy h;
+        up(h, most - 1);                           // uploads below 64 MiB, downloads into pages that are there below 4
+        for (int k = 0; k < 5; ++k) down(h, warm.data(), (4 << 20) - 1);
+        for (int k = 0; k < 7; ++k) down_new(h, 1 << 20);    // 7 MiB of those that gain
+        opened(false, false);
+        down_new(h, 1 << 20);
+        opened(false, true);
+        for (size_t n : {1048576u, 1048577u, 2097152u, 4194304u, 9000001u}) {
+            down(h, warm.data(), n);
+            down_new(h, n);
+        }
+        opened(false, true);
+    }
+    opened(false, false);
+    {
+        HostCopy h;
+        up(h, most);
+        opened(false, true);
+    }
+    opened(false, false);
+}
+""")
