@@ -1350,6 +1350,10 @@ __device__ __forceinline__ void persistent_body(const BatchTable *__restrict__ t
     if (work != nullptr) total = which == kListFirst ? q->survivors : which == 1 ? q->misfits : q->count[which];
     unsigned long long *const head = which == kListFirst ? &q->head : which == 1 ? &q->head_m : &q->next[which];
     if (few != 0 && total <= few) return;                  // few enough for k_whole
+    // A claim takes up to 64 machines, so a short list leaves most waves
+    // nothing to do but to queue up at its counter (8,192 waves and no machine:
+    // 115 us, 5 this way); four times those that find one stay in the race.
+    if (work != nullptr && 16ull * (static_cast<uint64_t>(blockIdx.x) * (blockDim.x / kWave) + wib) >= total) return;
 
     bool has = false, exhausted = false, fresh = false, cut = false;
     Regs r{};
