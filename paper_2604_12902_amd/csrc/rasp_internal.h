@@ -119,6 +119,13 @@ struct TraceArgs {
     uint32_t spread;                   // the waves it spreads a short one over,
     uint32_t slab;                     // the bytes of LDS of each,
     uint32_t already;                  // and the first pass's transitions
+    // Sorted survivors go to k_whole together where one in kJoinShare or more
+    // does not run in nodes and `join` lanes, one round of it, hold all of them
+    // (0: never): those few take a chain of it in any case, and beside them the
+    // rest takes no longer (plain-scale, 9,553 survivors of which 143 do not:
+    // 20,000 transitions 6.3 -> 2.9 ms; in slots 4.6).  fig1 and beaver, where
+    // none or few do not, stay in nodes.
+    uint32_t join;
     uint32_t *idx[9], *left[9];       // by list (left null: the budget less the first pass)
 };
 // Waves a block of k_trace (at most) and of k_whole.  One-wave blocks of a
@@ -138,6 +145,7 @@ constexpr uint32_t kTraceEvents = 24, kTraceEventsSh = 11;   // general steps (a
 constexpr uint32_t kTraceFulls = 2, kTraceFullsSh = 10;      // times its tables are full before it leaves
 constexpr uint32_t kLateEvents = 64, kLateEventsSh = 8;      // the same for kListLate
 constexpr uint32_t kLateFulls = 16, kLateFullsSh = 9;
+constexpr uint32_t kJoinShare = 64;
 constexpr uint32_t kTraceDense = 4;                          // machines a wave of those beside the rest
 constexpr uint32_t kTraceNodes = 16, kTraceData = 10;        // 7 waves a CU
 constexpr uint32_t kTraceNodes2 = 48, kTraceData2 = 40;      // 2 waves a CU

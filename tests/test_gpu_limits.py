@@ -56,3 +56,30 @@ def test_load_after_a_fetch_without_room(R, num_vms):
         want = oracle.run(then, 3000, threads=8)
         compare(got, want, mem=False)
         assert np.array_equal(got["mem_digest"], oracle.digest(want))
+
+
+def _mixed(num_vms, wander, n):
+    """Machines that run in nodes (a counted loop) and, every `wander`-th one
+    (0: none), machines that store through a moving address."""
+    LOAD, ADD, SUB, STORE, JPOS, JMP = 1, 2, 3, 4, 5, 8
+    progs = []
+    for k in range(num_vms):
+        if wander and k % wander == 0:
+            progs.append([LOAD, k % 9, STORE, 24 + k % 400, LOAD, 0, ADD, 7, ADD, 20, STORE, 7, JMP, 2,
+                          0, 0, 0, 0, 0, 0, 2])
+        else:
+            progs.append([LOAD, 20000 + k % 50, SUB, 21, STORE, 22, LOAD, 1, STORE, 21, LOAD, 0, ADD, 22, SUB, 21,
+                          STORE, 22, JPOS, 10, 0, 0, 0])
+    return W.from_programs(W.ISA_CLASSIC, progs, n, [[]] * num_vms, ell=0, s=1)
+
+
+# sorted survivors, with as many beside the nodes as send all of them to k_whole
+# (one in 64), fewer, and none; and more of them than one round of it holds
+@pytest.mark.parametrize("num_vms,wander", [(640, 64), (640, 100), (640, 0), (640, 1), (40000, 20)])
+def test_sorted_survivors_together_or_apart(R, num_vms, wander):
+    print("case: sorted", num_vms, wander, flush=True)
+    b = _mixed(num_vms, wander, 480)
+    with _context(R, dict(first_pass=64)) as c:
+        h = c.load(b)
+        c.run(h, 9000)
+        compare(c.fetch(h, mem=True), oracle.run(b, 9000, threads=8))
