@@ -146,6 +146,8 @@ constexpr uint32_t kTraceFulls = 2, kTraceFullsSh = 10;      // times its tables
 constexpr uint32_t kLateEvents = 64, kLateEventsSh = 8;      // the same for kListLate
 constexpr uint32_t kLateFulls = 16, kLateFullsSh = 9;
 constexpr uint32_t kJoinShare = 64;
+constexpr uint32_t kCrowdLeast = 8;    // machines of a wave from which on most of them may leave together,
+constexpr uint32_t kCrowdEvents = 8, kCrowdRate = 16;        // with 8 general steps and one in 16 transitions
 constexpr uint32_t kTraceDense = 4;                          // machines a wave of those beside the rest
 constexpr uint32_t kTraceNodes = 16, kTraceData = 10;        // 7 waves a CU
 constexpr uint32_t kTraceNodes2 = 48, kTraceData2 = 40;      // 2 waves a CU

@@ -2332,6 +2332,17 @@ __global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *_
                 ready = readyx;
                 halted = haltedx;
             }
+            // Where most machines of a well filled wave step in general, those
+            // leave at once: a wave waits for every lane that does (before the
+            // work queue has them, 198,543 machines that store through a moving
+            // address 3.3 -> 1.0 ms, 60,000 that read arrays 6.3 -> 0.35).
+            const uint32_t gen = tr.ev + (r.ell > kTapeLdsMax ? reads : 0u);
+            const bool bad = own && to == kNone && gen >= kCrowdEvents && gen * kCrowdRate > limit - left;
+            const uint32_t here = static_cast<uint32_t>(__popcll(__ballot(has)));
+            if (here >= kCrowdLeast && 2u * static_cast<uint32_t>(__popcll(__ballot(bad))) > here && bad) {
+                to = ta.often;
+                ready = false;
+            }
         }
         // ---- run macro steps: until few transitions are left to some lane,
         // which then waits for others to come as far ----

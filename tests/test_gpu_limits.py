@@ -83,3 +83,28 @@ def test_sorted_survivors_together_or_apart(R, num_vms, wander):
         h = c.load(b)
         c.run(h, 9000)
         compare(c.fetch(h, mem=True), oracle.run(b, 9000, threads=8))
+
+
+# waves most of whose machines step in general from the start on, and waves
+# with as many that do not; below and above the machines of a wave from which
+# on they leave together; one list of both kinds of memory
+@pytest.mark.parametrize("num_vms,wander,n", [(30000, 1, 480), (30000, 2, 480), (30000, 3, 480), (9000, 1, 480),
+                                              (30000, 1, 900), (16000, 2, 900)])
+def test_waves_of_machines_outside_nodes(R, num_vms, wander, n):
+    print("case: crowd", num_vms, wander, n, flush=True)
+    b = _mixed(num_vms, wander, n)
+    with _context(R, dict(first_pass=64)) as c:
+        h = c.load(b)
+        c.run(h, 8600)
+        compare(c.fetch(h, mem=True), oracle.run(b, 8600, threads=8))
+
+
+# machines that read a tape longer than 64 words in a loop, then run in nodes
+def test_waves_of_long_tapes(R):
+    LOAD, ADD, STORE, JPOS, READ, JMP = 1, 2, 4, 5, 6, 8
+    b = W.from_programs(W.ISA_CLASSIC, [[READ, 30, LOAD, 0, ADD, 30, JPOS, 0, LOAD, 1, ADD, 31, STORE, 31, JMP, 8]] * 30000,
+                        100 + 4 * 7, [[1] * 200 + [-1] * 3] * 30000, ell=203, s=1)
+    with _context(R, dict(first_pass=64)) as c:
+        h = c.load(b)
+        c.run(h, 8600)
+        compare(c.fetch(h, mem=True), oracle.run(b, 8600, threads=8))
