@@ -228,7 +228,7 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
 // (which 1: the work list is a hot-cell first pass's misfit list, counted by
 // q->misfits and claimed through q->head_m; kListGeneral, kListEnd: that
 // list, rest_left its machines' transitions to go; a list of at most `few`
-// machines is left alone)
+// machines is left alone, or with a cap one of more)
 // the trace kernel over list ta.in
 // whole memories in LDS, 2^sh lanes a wave, over list ta.in if it has at
 // most ta.few machines

@@ -1349,7 +1349,9 @@ __device__ __forceinline__ void persistent_body(const BatchTable *__restrict__ t
     // the rest by the trace kernel), and its claim counter
     if (work != nullptr) total = which == kListFirst ? q->survivors : which == 1 ? q->misfits : q->count[which];
     unsigned long long *const head = which == kListFirst ? &q->head : which == 1 ? &q->head_m : &q->next[which];
-    if (few != 0 && total <= few) return;                  // few enough for k_whole
+    // few enough for k_whole; a pass that runs machines a part of the way (cap)
+    // is for lists of at most `few`
+    if (few != 0 && (cap == kNoCap ? total <= few : total > few)) return;
     // A claim takes up to 64 machines, so a short list leaves most waves
     // nothing to do but to queue up at its counter (8,192 waves and no machine:
     // 115 us, 5 this way); four times those that find one stay in the race.

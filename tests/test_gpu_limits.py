@@ -108,3 +108,16 @@ def test_waves_of_long_tapes(R):
         h = c.load(b)
         c.run(h, 8600)
         compare(c.fetch(h, mem=True), oracle.run(b, 8600, threads=8))
+
+
+# memories in HBM, a budget below that of traces: survivor lists of up to two
+# rounds of k_whole run their transients in a pass of their own, longer ones do
+# not (16,384 on 256 CUs at n = 1,024: 57,000 machines of this population)
+@pytest.mark.parametrize("num_vms", [40000, 57000, 90000])
+def test_passes_before_short_and_long_lists(R, num_vms):
+    print("case: passes", num_vms, flush=True)
+    b = W.config3(num_vms=num_vms, seed=34)
+    with _context(R, dict(first_pass=64)) as c:
+        h = c.load(b)
+        c.run(h, 1500)
+        compare(c.fetch(h, mem=True), oracle.run(b, 1500, threads=8))
