@@ -1107,6 +1107,12 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 const uint64_t blocks_t = std::min<uint64_t>((total + wpb_t - 1) / wpb_t, on_cus);
                 return launch_trace(dt2, ran, isa, wm, ta, wpb_t, static_cast<uint32_t>(blocks_t), qs, on);
             };
+            // the work queue of what neither k_trace nor k_whole takes: in slots
+            // as without traces; with hot cells, whose slots are their tables',
+            // memories in HBM as a hot-cell first pass's misfits
+            const bool slots = S_hot == 0;
+            const uint32_t P_q = slots ? P : 0u, wpb_q = slots ? wpb : 4u;
+            const uint32_t blocks_q = slots ? blocks : resident_blocks(c, 4u, 0u, waves);
             auto queue = [&](uint32_t in, uint32_t Pw, uint32_t wpbw, uint32_t blocksw, uint32_t few, hipStream_t on) {
                 return launch_persistent(dt2, total, ta.idx[in], ran, isa, pow2, wm, epoch, Pw, max_n, max_ell, wpbw, blocksw,
                                          kNoCap, nullptr, qs, on, in, ta.left[in], few);
@@ -1117,7 +1123,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 uint32_t few;
                 const hipError_t e = whole(dt2, ta, in, kWholeRounds, &few, on);
                 if (e) return e;
-                return queue(in, P, wpb, blocks, few, on);
+                return queue(in, P_q, wpb_q, blocks_q, few, on);
             };
             if ((rc = ensure_stream2(c)) || (rc = ensure_stream3(c))) return rc;
             hipStream_t st2 = c->stream2, st3 = c->stream3;

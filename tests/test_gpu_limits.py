@@ -121,3 +121,17 @@ def test_passes_before_short_and_long_lists(R, num_vms):
         h = c.load(b)
         c.run(h, 1500)
         compare(c.fetch(h, mem=True), oracle.run(b, 1500, threads=8))
+
+
+# more machines outside nodes than k_whole takes in a context with hot cells:
+# the work queue steps them in HBM, whatever the slots
+@pytest.mark.parametrize("num_vms,n,lds_words", [(40000, 900, 40), (70000, 480, 0), (70000, 480, 480)])
+def test_work_queue_of_a_hot_cell_context(R, num_vms, n, lds_words):
+    print("case: hot cells", num_vms, n, lds_words, flush=True)
+    b = _mixed(num_vms, 1, n)
+    with _context(R, dict(first_pass=576, lds_words=lds_words)) as c:
+        c.set(R.RASP_OPT_HOT_CELLS, 32)
+        c.set(R.RASP_OPT_PROFILE_STEPS, 512)
+        h = c.load(b)
+        c.run(h, 8900)
+        compare(c.fetch(h, mem=True), oracle.run(b, 8900, threads=8))
