@@ -302,7 +302,7 @@ def TUNED_OPTIONS(R):
     """The context options the autotuner chooses (copied to in-flight contexts)."""
     return (R.RASP_OPT_SCHEDULE, R.RASP_OPT_LDS_WORDS, R.RASP_OPT_FIRST_PASS, R.RASP_OPT_EPOCH,
             R.RASP_OPT_WAVES_PER_CU, R.RASP_OPT_FIRST_PASS_KIND, R.RASP_OPT_HOT_CELLS,
-            R.RASP_OPT_PROFILE_STEPS, R.RASP_OPT_MISFIT_WAVES)
+            R.RASP_OPT_PROFILE_STEPS, R.RASP_OPT_MISFIT_WAVES, R.RASP_OPT_TRACES)
 
 
 def current_knobs(R, ctx, lazy):
@@ -566,6 +566,7 @@ def main():
             ctx.set(R.RASP_OPT_HOT_CELLS, tuned.get("hot_cells", 0))
             ctx.set(R.RASP_OPT_PROFILE_STEPS, tuned.get("profile_steps", 256))
             ctx.set(R.RASP_OPT_MISFIT_WAVES, tuned.get("misfit_waves", 6))
+            ctx.set(R.RASP_OPT_TRACES, tuned.get("traces", 1))
         ctx.set(R.RASP_OPT_SCHEDULE, schedule)
         if args.first_pass is not None:
             ctx.set(R.RASP_OPT_FIRST_PASS, args.first_pass)

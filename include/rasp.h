@@ -388,6 +388,11 @@ int rasp_free_batch(rasp_ctx *ctx, rasp_batch b);
  *                          cells do not fit (memory in HBM, on a second stream
  *                          of the context beside the fits' launch), 1..32
  *                          (default 6)
+ *   RASP_OPT_TRACES        1 (default): a first pass's survivors are compiled
+ *                          into traces where RASP_OPT_FIRST_PASS says; 0: never
+ *   RASP_OPT_ROUTE         read only: the RASP_ROUTE_* bits of the way the
+ *                          context's latest run was launched (a replayed graph:
+ *                          as captured); after rasp_autotune, of all its trials
  */
 enum {
     RASP_OPT_SCHEDULE = 1,
@@ -399,7 +404,20 @@ enum {
     RASP_OPT_FIRST_PASS_KIND = 8,
     RASP_OPT_HOT_CELLS = 9,
     RASP_OPT_PROFILE_STEPS = 10,
-    RASP_OPT_MISFIT_WAVES = 11
+    RASP_OPT_MISFIT_WAVES = 11,
+    RASP_OPT_TRACES = 12,
+    RASP_OPT_ROUTE = 13
+};
+/* bits of RASP_OPT_ROUTE */
+enum {
+    RASP_ROUTE_FIRST = 1,          /* a first pass                               */
+    RASP_ROUTE_DIRECT = 2,         /* every machine whole in LDS, no first pass  */
+    RASP_ROUTE_WHOLE = 4,          /* survivors whole in LDS if they are few     */
+    RASP_ROUTE_PASS = 8,           /* survivors' transients in a pass of their own */
+    RASP_ROUTE_TRACES = 16,        /* survivors compiled into traces             */
+    RASP_ROUTE_SORTED = 32,        /* these sorted first                         */
+    RASP_ROUTE_HOT_CELLS = 64,     /* hot-cell tables                            */
+    RASP_ROUTE_NO_ROOM = 128       /* no traces for want of room in the arena    */
 };
 enum { RASP_SCHED_AUTO = 0, RASP_SCHED_PLAIN = 1, RASP_SCHED_PERSISTENT = 2 };
 
@@ -434,7 +452,10 @@ int rasp_kernel_times(rasp_ctx *ctx, double *ms, uint64_t *launches);
  * first-pass length, epoch, waves per compute unit, first-pass kind), then
  * hot-cell tables (slots per machine and misfit waves per CU on a grid, then
  * the profile length) when memories have at most 2,048 words, and the plain
- * schedule; keeps the fastest setting in the context and writes it to
+ * schedule.  Where a run of all of b would compile its survivors (RASP_OPT_TRACES),
+ * the search is made with traces and again without, hot cells in the second
+ * only.  What a run chooses by the number of its machines a trial chooses by
+ * b's.  Keeps the fastest setting in the context (RASP_OPT_TRACES too) and writes it to
  * chosen[0..8] = {schedule, lds_words, first_pass, epoch, waves_per_cu,
  * first_pass_kind, hot_cells, profile_steps, misfit_waves} (chosen may be
  * NULL); a knob leaves its current setting only for a setting at least 3%

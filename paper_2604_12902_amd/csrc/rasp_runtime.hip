@@ -184,6 +184,9 @@ struct rasp_ctx {
     int64_t hot_cells = 0;               // slots of a hot-cell table (0: off)
     int64_t profile_steps = 256;         // transitions profiled at the end of a hot-cell first pass
     int64_t misfit_waves = 6;            // waves per CU of the hot-cell misfits' launch
+    int64_t traces = 1;                  // survivors may be compiled into traces
+    int64_t route = 0;                   // RASP_ROUTE_* of the latest run
+    uint64_t plan_total = 0;             // autotune trials: machines of the batch the trial's prefix stands for
     Alloc hot;                           // hot-cell multipliers, tags and misfit list
     uint64_t hot_cap = 0, hot_S = 0;
     // second stream (same CU mask as the first) and its two events: the
@@ -222,6 +225,7 @@ struct rasp_ctx {
         std::vector<uint64_t> handles;
         Alloc table;                       // the graph's own device batch table
         hipGraphExec_t exec = nullptr;
+        int64_t route = 0;
     };
     std::vector<GraphEntry> graphs;
     // kernel timing (RASP_OPT_PROFILE)
@@ -679,6 +683,9 @@ int ensure_work(rasp_ctx *c, uint64_t items)
     return RASP_OK;
 }
 
+// the trace kernel's lists of `items` machines
+uint64_t trace_bytes(uint64_t items) { return 13 * align_up(4 * items, kAlign); }
+
 // room for the trace kernel's lists of `items` machines; false: none, and the
 // run goes without traces
 bool ensure_trace(rasp_ctx *c, uint64_t items)
@@ -689,7 +696,7 @@ bool ensure_trace(rasp_ctx *c, uint64_t items)
         arena_free(c, &c->trace);
     }
     c->trace_cap = 0;
-    if (!arena_alloc(c, 13 * align_up(4 * items, kAlign), &c->trace)) return false;
+    if (!arena_alloc(c, trace_bytes(items), &c->trace)) return false;
     c->trace_cap = items;
     return true;
 }
@@ -841,6 +848,8 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             if (rc) return rc;
         }
     }
+    int64_t &route = c->route;
+    if (c->plan_total == 0) route = 0;
     // queue counters: the context's, or the caller-independent scratch
     QueueState *const qs = rs ? rs->queue : c->queue;
     const bool graphed = c->graph && !any_fresh && !rs && c->hot_cells == 0;
@@ -912,8 +921,13 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
     const WholeShape ws = whole_shape(max_n, total, lds, static_cast<uint32_t>(c->cus));
     const uint32_t sh = ws.sh, slab = ws.slab, blocks_w = ws.blocks;
     const bool whole_ok = blocks_w != 0;
+    // lanes of one round; in an autotune trial those of the whole batch, and as
+    // many fewer for the trial's part of it
+    const uint64_t plan = std::max(total, c->plan_total);
+    const uint64_t lanes_w = static_cast<uint64_t>(kWholeWpb * whole_shape(max_n, plan, lds, static_cast<uint32_t>(c->cus)).blocks) << sh;
+    const uint32_t round_w = static_cast<uint32_t>(lanes_w * total / plan);
     auto whole = [&](const BatchTable *tb, TraceArgs wa, uint32_t in, uint32_t rounds, uint32_t *few, hipStream_t on) {
-        *few = whole_ok ? rounds * (kWholeWpb * blocks_w << sh) : 0;
+        *few = whole_ok ? std::max(1u, rounds * round_w) : 0;
         if (!whole_ok) return hipSuccess;
         wa.in = in;
         wa.few = *few;
@@ -945,6 +959,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             if (cap > 0 && cap < maxb && (rc = ensure_work(c, total))) return rc;
             rasp_ctx::GraphEntry g;
             g.key = key;
+            if (cap > 0 && cap < maxb) g.route = RASP_ROUTE_FIRST | (whole_ok ? RASP_ROUTE_WHOLE : 0);
             if (!arena_alloc(c, sizeof(BatchTable), &g.table)) return fail(c, RASP_E_NOMEM, "arena cannot hold a graph table");
             BatchTable *gt = at<BatchTable>(c, g.table);
             HIPCHK(c, hipMemcpyAsync(gt, ht, sizeof(BatchTable), hipMemcpyHostToDevice, st));
@@ -975,21 +990,24 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             ge = &c->graphs.back();
         }
         hipGraphExec_t ex = ge->exec;
+        route |= ge->route;
         HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] { return hipGraphLaunch(ex, st); }));
         return RASP_OK;
     }
     // traces: survivors with a budget worth compiling for, in a launch that may allocate
-    const bool trace = sched == RASP_SCHED_PERSISTENT && cap > 0 && cap < maxb &&
-                       maxb - cap >= kTraceMinLeft &&
-                       max_n <= kTraceMaxN && rs == nullptr && ensure_work(c, total) == RASP_OK && ensure_trace(c, total);
+    const bool worth = sched == RASP_SCHED_PERSISTENT && c->traces != 0 && cap > 0 && cap < maxb &&
+                       maxb - cap >= kTraceMinLeft && max_n <= kTraceMaxN && rs == nullptr;
+    const bool trace = worth && ensure_work(c, total) == RASP_OK && ensure_trace(c, total);
+    if (worth && !trace) route |= RASP_ROUTE_NO_ROOM;
     // A batch of a few machines a wave runs whole in LDS from the start: the
     // first pass takes as long for it as for a hundred thousand (64 transitions
     // in HBM, 42 us of 1,024 machines' 195) and retires no more than the lanes
     // beside it wait for.
     const bool direct = sched == RASP_SCHED_PERSISTENT && cap > 0 && cap < maxb && !lds_first && !any_fresh && !trace &&
                         !hot && rs == nullptr && whole_ok &&
-                        total <= std::min<uint64_t>(kWholeWpb * blocks_w << sh, static_cast<uint64_t>(kWholeAll) * kWholeWpb * c->cus);
+                        plan <= std::min<uint64_t>(lanes_w, static_cast<uint64_t>(kWholeAll) * kWholeWpb * c->cus);
     if (direct) {
+        route |= RASP_ROUTE_DIRECT;
         TraceArgs wa{};
         wa.all = static_cast<uint32_t>(total);
         uint32_t few;
@@ -1003,6 +1021,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
         // hot-cell first pass (plain, profiling its last transitions), then
         // the persistent kernel over fits and misfits with their LDS tables
         if ((rc = ensure_work(c, total)) || (rc = ensure_hot(c, total, S_hot))) return rc;
+        route |= RASP_ROUTE_FIRST | RASP_ROUTE_HOT_CELLS;
         uint32_t *work = at<uint32_t>(c, c->work);
         HotArgs ha{};
         ha.S = S_hot;
@@ -1053,6 +1072,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             return rc;
         }
         uint32_t *work = rs ? rs->work : at<uint32_t>(c, c->work);
+        route |= RASP_ROUTE_FIRST;
         if (lds_first) {
             HIPCHK(c, timed_launch(c, RASP_KERNEL_FIRST, [&] {
                 return launch_persistent(dt, total, nullptr, 0, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, cap, work, qs, st); }));
@@ -1096,6 +1116,8 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             const bool sort = max_n <= kSortMaxN;
             const bool warm = !sort && cap < kTraceWarm && maxb > kTraceWarm;
             const uint32_t from = warm ? kListWarm : kListFirst, ran = warm ? kTraceWarm : cap;
+            route |= RASP_ROUTE_TRACES | (sort ? RASP_ROUTE_SORTED : 0) | (warm ? RASP_ROUTE_PASS : 0) |
+                     (whole_ok ? RASP_ROUTE_WHOLE : 0);
             const uint32_t cus = static_cast<uint32_t>(c->cus);
             auto traces = [&](uint32_t in, bool large, uint32_t often, uint32_t full, uint32_t on_cus, hipStream_t on) {
                 ta.in = in;
@@ -1146,7 +1168,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                     if (!e) e = hipEventRecord(c->ev_first, st);
                     if (!e) e = hipStreamWaitEvent(st2, c->ev_first, 0);
                     if (!e) e = hipStreamWaitEvent(st3, c->ev_first, 0);
-                    ta.join = whole_ok ? kWholeWpb * blocks_w << sh : 0;
+                    ta.join = round_w;
                     if (!e) e = timed_launch(c, RASP_KERNEL_MISFIT, [&] { return general(kListGeneral, st2); }, st2);
                     if (!e) e = hipEventRecord(c->ev_second, st2);
                     const uint32_t join = ta.join;
@@ -1194,9 +1216,10 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             // the pass, 2.60 without).
             const bool warm = rs == nullptr && sched == RASP_SCHED_PERSISTENT && P < max_n && whole_ok && cap < kTraceWarm &&
                               maxb - cap >= kWarmMinLeft && ensure_trace(c, total);
+            route |= (warm ? RASP_ROUTE_PASS : 0) | (whole_ok ? RASP_ROUTE_WHOLE : 0);
             HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
                 if (!warm) return survivors(dt2, work, kListFirst, cap);
-                const uint32_t most = 2 * (kWholeWpb * blocks_w << sh);
+                const uint32_t most = std::max(1u, 2 * round_w);
                 uint32_t *list = at<uint32_t>(c, c->trace);
                 hipError_t e = launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
                                                  kTraceWarm - cap, list, qs, st, kListFirst, nullptr, most);
@@ -1905,6 +1928,11 @@ int rasp_set_option(rasp_ctx *c, int option, int64_t value)
     case RASP_OPT_MISFIT_WAVES:
         if (value < 1 || value > 32) return fail(c, RASP_E_INVAL, "misfit waves per CU must be in [1, 32]");
         c->misfit_waves = value; return RASP_OK;
+    case RASP_OPT_TRACES:
+        if (value != 0 && value != 1) return fail(c, RASP_E_INVAL, "traces must be 0 or 1");
+        c->traces = value; return RASP_OK;
+    case RASP_OPT_ROUTE:
+        return fail(c, RASP_E_INVAL, "the route is read only");
     default:
         return fail(c, RASP_E_INVAL, "unknown option %d", option);
     }
@@ -1925,6 +1953,8 @@ int rasp_get_option(rasp_ctx *c, int option, int64_t *value)
     case RASP_OPT_HOT_CELLS: *value = c->hot_cells; return RASP_OK;
     case RASP_OPT_PROFILE_STEPS: *value = c->profile_steps; return RASP_OK;
     case RASP_OPT_MISFIT_WAVES: *value = c->misfit_waves; return RASP_OK;
+    case RASP_OPT_TRACES: *value = c->traces; return RASP_OK;
+    case RASP_OPT_ROUTE: *value = c->route; return RASP_OK;
     default: return fail(c, RASP_E_INVAL, "unknown option %d", option);
     }
 }
@@ -1948,8 +1978,9 @@ int rasp_kernel_times(rasp_ctx *c, double *ms, uint64_t *launches)
     return RASP_OK;
 }
 
-// knobs the autotuner chooses, in the order of its `chosen` array
-constexpr int kTuneKnobs = 9;
+// knobs the autotuner chooses: those of its `chosen` array in its order, and
+// RASP_OPT_TRACES
+constexpr int kTuneChosen = 9, kTuneKnobs = kTuneChosen + 1;
 
 // a knob moves away from the current setting only for a trial at least 3%
 // faster: timings of near-equal settings differ by noise from run to run
@@ -1979,6 +2010,16 @@ int rasp_autotune(rasp_ctx *c, rasp_batch h, uint64_t budget, uint64_t max_vms, 
     HIPCHK(c, hipMemcpyAsync(&ss, b->dev.s + K - 1, 4, hipMemcpyDeviceToHost, st));
     HIPCHK(c, hipStreamSynchronize(st));
     const uint64_t m_end = mo + ((nn + 3ull) & ~3ull), t_end = to + el, y_end = yo + ss;
+    // would a run of the whole batch compile its survivors: by the budget, the
+    // memories and the room the arena has now (the copies below take of it)
+    bool want = c->traces != 0 && b->max_n <= kTraceMaxN && bud > kTraceMinLeft + 64;
+    if (want) {
+        Alloc list, lists;
+        want = (b->N <= c->work_cap || arena_alloc(c, 4 * b->N, &list)) &&
+               (b->N <= c->trace_cap || arena_alloc(c, trace_bytes(b->N), &lists));
+        arena_free(c, &list);
+        arena_free(c, &lists);
+    }
     // snapshot (restore source) and trial batch, both K machines; a lazy
     // batch needs no snapshot (its c0 is rebuilt from the descriptor)
     Batch snap, trial;
@@ -2039,7 +2080,7 @@ int rasp_autotune(rasp_ctx *c, rasp_batch h, uint64_t budget, uint64_t max_vms, 
     if (e) { release(); return fail(c, RASP_E_DEVICE, "autotune snapshot: %s", hipGetErrorString(e)); }
     const int64_t saved[] = {c->schedule, c->lds_words, c->first_pass, c->epoch, c->waves_per_cu,
                              c->first_pass_kind, c->hot_cells, c->profile_steps, c->misfit_waves,
-                             c->graph, c->profile};
+                             c->traces, c->graph, c->profile};
     c->graph = 0;
     c->profile = 0;
     hipEvent_t e0, e1;
@@ -2090,28 +2131,46 @@ int rasp_autotune(rasp_ctx *c, rasp_batch h, uint64_t budget, uint64_t max_vms, 
     int64_t cur[kTuneKnobs] = {RASP_SCHED_PERSISTENT,
                                c->lds_words < 0 ? static_cast<int64_t>(lds_words_for(c, b->max_n, b->max_ell)) : c->lds_words,
                                c->first_pass, c->epoch, c->waves_per_cu, c->first_pass_kind, 0, c->profile_steps,
-                               c->misfit_waves};
+                               c->misfit_waves, c->traces};
     auto apply = [&](const int64_t *o) {
         c->schedule = o[0]; c->lds_words = o[1]; c->first_pass = o[2]; c->epoch = o[3]; c->waves_per_cu = o[4];
         c->first_pass_kind = o[5]; c->hot_cells = o[6]; c->profile_steps = o[7]; c->misfit_waves = o[8];
+        c->traces = o[9];
     };
     // one coordinate search (LDS words, first-pass length, epoch, waves per
-    // CU) for each first-pass kind, from the same start; the kinds interact
-    // with every other knob, so they are not searched one after the other
+    // CU) for each first-pass kind, with traces and without where a run would
+    // take them, all from the same start; kinds and traces interact with every
+    // other knob, so they are not searched one after the other
     int64_t start[kTuneKnobs];
     for (int q = 0; q < kTuneKnobs; ++q) start[q] = cur[q];
     const std::vector<int64_t> *lists[5] = {nullptr, &lds_c, &fp_c, &ep_c, &wv_c};
     double best = 1e30;
-    bool warm = false;
-    for (int64_t kind : fk_c) {
+    // warm-up run, which shows whether the trials have room for traces
+    c->plan_total = b->N;
+    c->route = 0;
+    {
+        int64_t o[kTuneKnobs];
+        for (int q = 0; q < kTuneKnobs; ++q) o[q] = start[q];
+        if (o[2] <= 0 || o[2] + static_cast<int64_t>(kTraceMinLeft) > bud) o[2] = 64;
+        o[5] = fk_c[0];
+        apply(o);
+        double ms = 0;
+        rc = trial_ms(&ms);
+    }
+    const bool traced = want && (c->route & RASP_ROUTE_TRACES) != 0;
+    std::vector<std::pair<int64_t, int64_t>> searches;       // traces, first-pass kind
+    for (int64_t kind : fk_c) searches.push_back({start[9], kind});
+    if (traced)
+        for (int64_t kind : fk_c) searches.push_back({0, kind});
+    for (auto [with, kind] : searches) {
         if (rc) break;
         int64_t kc[kTuneKnobs];
         for (int q = 0; q < kTuneKnobs; ++q) kc[q] = start[q];
         kc[5] = kind;
+        kc[9] = with;
         double kbest = 1e30;
         apply(kc);
-        if (!warm) { rc = trial_ms(&kbest); warm = true; }     // warm-up run
-        if (!rc) rc = trial_ms(&kbest);
+        rc = trial_ms(&kbest);
         for (int knob = 1; knob <= 4 && !rc; ++knob) {
             for (int64_t val : *lists[knob]) {
                 if (val == kc[knob]) continue;
@@ -2138,8 +2197,10 @@ int rasp_autotune(rasp_ctx *c, rasp_batch h, uint64_t budget, uint64_t max_vms, 
     // hot-cell tables (memories of at most kHotMaxN words, a budget beyond
     // the profiled first pass): slots per machine and the misfits' waves per
     // CU on a grid, then the profile length for the best of them; each
-    // against the best setting so far
-    if (!rc && b->max_n <= kHotMaxN && bud > 2048) {
+    // against the best setting so far, and without traces, which would run in
+    // their place (left out where a run takes traces and the trials have no
+    // room for them: nothing here is what it would be measured against)
+    if (!rc && b->max_n <= kHotMaxN && bud > 2048 && want == traced) {
         int64_t hb[kTuneKnobs];
         double hbest = 1e30;
         for (int64_t S : {16, 32}) {
@@ -2148,6 +2209,7 @@ int rasp_autotune(rasp_ctx *c, rasp_batch h, uint64_t budget, uint64_t max_vms, 
                 for (int q = 0; q < kTuneKnobs; ++q) o[q] = cur[q];
                 o[0] = RASP_SCHED_PERSISTENT; o[2] = 576; o[5] = 0; o[6] = S; o[7] = 512; o[8] = mw;
                 o[4] = 16;
+                if (traced) o[9] = 0;
                 apply(o);
                 double ms = 0;
                 if ((rc = trial_ms(&ms))) break;
@@ -2183,14 +2245,15 @@ int rasp_autotune(rasp_ctx *c, rasp_batch h, uint64_t budget, uint64_t max_vms, 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     release();
-    c->graph = saved[9];
-    c->profile = saved[10];
+    c->plan_total = 0;
+    c->graph = saved[10];
+    c->profile = saved[11];
     if (rc) {
         apply(saved);
         return rc;
     }
     apply(cur);
-    if (chosen) for (int q = 0; q < kTuneKnobs; ++q) chosen[q] = cur[q];
+    if (chosen) for (int q = 0; q < kTuneChosen; ++q) chosen[q] = cur[q];
     if (best_ms) *best_ms = best;
     return RASP_OK;
 }

@@ -40,6 +40,10 @@ RASP_OPT_FIRST_PASS_KIND = 8
 RASP_OPT_HOT_CELLS = 9
 RASP_OPT_PROFILE_STEPS = 10
 RASP_OPT_MISFIT_WAVES = 11
+RASP_OPT_TRACES = 12
+RASP_OPT_ROUTE = 13
+RASP_ROUTE_FIRST, RASP_ROUTE_DIRECT, RASP_ROUTE_WHOLE, RASP_ROUTE_PASS = 1, 2, 4, 8
+RASP_ROUTE_TRACES, RASP_ROUTE_SORTED, RASP_ROUTE_HOT_CELLS, RASP_ROUTE_NO_ROOM = 16, 32, 64, 128
 KERNEL_NAMES = ("pack", "plain", "persistent", "digest", "other", "first", "misfit")
 
 EXPORTED = ("rasp_create", "rasp_create_on_cus", "rasp_destroy", "rasp_last_error", "rasp_batch_footprint",
@@ -359,11 +363,13 @@ AUTOTUNE_KNOBS = ("schedule", "lds_words", "first_pass", "epoch", "waves_per_cu"
 
 
 def rasp_autotune(ctx, batch: int, budget: int, max_vms: int = 0) -> dict:
-    """Pick and set the scheduling knobs for batches shaped like `batch`."""
+    """Pick and set the scheduling knobs for batches shaped like `batch`; the
+    dict also holds "traces", RASP_OPT_TRACES as it was left."""
     chosen = np.zeros(len(AUTOTUNE_KNOBS), np.int64)
     best = ctypes.c_double()
     _check(_lib.rasp_autotune(ctx, batch, budget, max_vms, _ptr(chosen), ctypes.byref(best)), ctx)
     out = {k: int(v) for k, v in zip(AUTOTUNE_KNOBS, chosen)}
+    out["traces"] = rasp_get_option(ctx, RASP_OPT_TRACES)
     out["best_ms"] = best.value
     return out
 
