@@ -1,27 +1,27 @@
 // Copies between ordinary (pageable) host memory and the device, through a
 // context's own pinned memory.
 //
-// hipMemcpyAsync on pageable memory moves it through the runtime's staging
-// buffer on the calling thread, and waits.  That is 30 GB/s up and 17 down, but
-// 4 down into memory the caller has just allocated, whose pages the copy
-// touches first.  Large copies down go in chunks: kWorkers threads (the caller
-// and its helpers) claim them in turn; each keeps two pinned chunks, so its own
-// copy in host memory overlaps the device's, and the pages are touched by all
-// of them.  Small copies (at most 256 KiB) of one call go through one pinned
-// area, without a wait for each.
+// hipMemcpyAsync on pageable memory moves it through a staging buffer of the
+// stream, on the calling thread, and waits.  The first 16 MiB over a stream go
+// at 2.6 GB/s (1 MiB 390 us, 51 later: the buffer's pages are touched for the
+// first time), and copies down into memory the caller has just allocated, whose
+// pages are touched too, at 4 GB/s.  Here copies of up to 1 MiB go through one
+// pinned area, several of a call without a wait for each (1 MiB 51 us up, 60
+// down).  Larger ones go in chunks: kWorkers threads (the caller and its
+// helpers) claim them in turn; each keeps two pinned chunks, so its own copy in
+// host memory overlaps the device's, and pages are touched by all of them (1 MiB
+// 94-120 us, 4 MiB 216 up, 240 down and 460 into new pages, where one thread
+// takes 130, 240 and 980 once its buffer has been touched).
 #ifndef RASP_HOSTCOPY_H
 #define RASP_HOSTCOPY_H
 
 #include <hip/hip_runtime.h>
-#include <sys/mman.h>
-#include <unistd.h>
 
 #include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <cstdint>
 #include <cstring>
-#include <initializer_list>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -32,17 +32,12 @@ class HostCopy {
 public:
     static constexpr uint32_t kWorkers = 4, kSlots = 2;
     static constexpr uint64_t kChunk = 1ull << 20, kChunkMin = 256ull << 10;
-    // Smallest copies that go in chunks (a helper wakes in some 30 us), plain
-    // against chunks: down into new pages 1 MiB 241 us against 207, 4 MiB 982
-    // against 518; into pages that are there 3 MiB 183 against 224, 4 MiB 242
-    // against 245, 8 MiB 476 against 340; up 16 MiB 459 against 575, 64 MiB 2258
-    // against 2152.
-    static constexpr uint64_t kMinNew = 1ull << 20, kMinDown = 4ull << 20, kMinUp = 64ull << 20;
-    // Chunks and helpers take some 1 ms to make, which is what they gain over
-    // 8 MiB: they are made once copies of that size have been.
-    static constexpr uint64_t kOpenAfter = 8ull << 20;
-    // the pinned area of small copies, and the largest of them
-    static constexpr uint64_t kArea = 1ull << 20, kSmall = 256ull << 10;
+    // the pinned area, and so the largest copy that does not go in chunks
+    static constexpr uint64_t kArea = 1ull << 20;
+    // Chunks and helpers take some 0.5 ms to make and 0.1 to end: they are made
+    // at the first copy that goes in them, or before it once this much has been
+    // copied, which a context for a small batch or two does not come to.
+    static constexpr uint64_t kOpenAfter = 512ull << 10;
 
     ~HostCopy() { close(); }
 
@@ -66,7 +61,9 @@ public:
     // A copy to the device whose source may be reused on return.
     hipError_t put(int device, void *dst, const void *src, uint64_t bytes, hipStream_t st)
     {
-        char *p = take(bytes, st);
+        hipError_t e = hipSuccess;
+        char *p = take(device, bytes, st, &e);
+        if (e) return e;
         if (!p) return copy(device, dst, src, bytes, hipMemcpyHostToDevice, st);
         std::memcpy(p, src, bytes);
         return hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, st);
@@ -75,9 +72,11 @@ public:
     // A copy from the device whose data is there after flush().
     hipError_t get(int device, void *dst, const void *src, uint64_t bytes, hipStream_t st)
     {
-        char *p = take(bytes, st);
+        hipError_t e = hipSuccess;
+        char *p = take(device, bytes, st, &e);
+        if (e) return e;
         if (!p) return copy(device, dst, src, bytes, hipMemcpyDeviceToHost, st);
-        const hipError_t e = hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToHost, st);
+        e = hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToHost, st);
         if (!e) got_.push_back({dst, p, bytes});
         return e;
     }
@@ -99,8 +98,7 @@ public:
     {
         if (bytes == 0) return hipSuccess;
         const bool up = kind == hipMemcpyHostToDevice;
-        if (bytes < kMinNew || !(up || kind == hipMemcpyDeviceToHost) ||
-            bytes < (up ? kMinUp : present(dst, bytes) ? kMinDown : kMinNew) || pinned(up ? src : dst) || !open(device, bytes))
+        if (bytes <= kArea || !(up || kind == hipMemcpyDeviceToHost) || pinned(up ? src : dst) || !open(device))
             return hipMemcpyAsync(dst, src, bytes, kind, st);
         const uint64_t chunk = std::min<uint64_t>(kChunk, std::max<uint64_t>(kChunkMin, (bytes / (kWorkers * kSlots) + 4095) & ~4095ull));
         {
@@ -162,12 +160,15 @@ private:
         chunks_ = nullptr;
     }
 
-    // `bytes` of the area, or null; the area is made at the first small copy
-    char *take(uint64_t bytes, hipStream_t st)
+    // `bytes` of the area, or null; the area is made at the first such copy, and
+    // the stream waited for when it is used up
+    char *take(int device, uint64_t bytes, hipStream_t st, hipError_t *e)
     {
         const uint64_t n = (bytes + 255) & ~255ull;
-        if (bytes == 0 || bytes > kSmall || used_ + n > kArea || (!area_ && !open_area()) || got_.size() == got_.capacity())
-            return nullptr;
+        if (bytes == 0 || bytes > kArea || (!area_ && !open_area())) return nullptr;
+        moved_ += bytes;
+        if (moved_ > kOpenAfter) (void)open(device);
+        if ((used_ + n > kArea || got_.size() == got_.capacity()) && (*e = flush(st))) return nullptr;
         char *p = area_ + used_;
         used_ += n;
         on_ = st;
@@ -206,24 +207,11 @@ private:
         return a.type != hipMemoryTypeUnregistered;
     }
 
-    // are the pages of this memory there already (by its first, middle and last)
-    static bool present(const void *p, uint64_t bytes)
-    {
-        const uint64_t page = static_cast<uint64_t>(sysconf(_SC_PAGESIZE)), a = reinterpret_cast<uint64_t>(p);
-        for (uint64_t at : {a, a + bytes / 2, a + bytes - 1}) {
-            unsigned char in = 1;
-            if (mincore(reinterpret_cast<void *>(at / page * page), 1, &in) == 0 && !(in & 1)) return false;
-        }
-        return true;
-    }
-
     // the chunks and the helpers
-    bool open(int device, uint64_t bytes)
+    bool open(int device)
     {
         if (chunks_) return true;
         if (failed_) return false;
-        wanted_ += bytes;
-        if (wanted_ < kOpenAfter) return false;
         failed_ = true;
         device_ = device;
         if (!(chunks_ = host_malloc(kWorkers * kSlots * kChunk))) return false;
@@ -314,8 +302,8 @@ private:
 
     int device_ = 0;
     char *chunks_ = nullptr, *area_ = nullptr;
-    uint64_t wanted_ = 0;                // bytes that would have gone in chunks so far
     bool failed_ = false, no_area_ = false;      // tried already (null: without success)
+    uint64_t moved_ = 0;                 // bytes copied by way of the area
     Slot slots_[kWorkers][kSlots];
     uint64_t used_ = 0;                  // of the area, by copies on the stream
     hipStream_t on_ = nullptr;

@@ -36,6 +36,7 @@ struct Model {
     std::map<char *, size_t> pinned;
     size_t pinned_bytes = 0;
     int events = 0;
+    bool refuse = false;                 // no pinned memory
     bool is_pinned(const void *p)
     {
         auto it = pinned.upper_bound(static_cast<char *>(const_cast<void *>(p)));
@@ -56,6 +57,7 @@ inline hipError_t hipGetLastError() { return hipSuccess; }
 inline hipError_t hipHostMalloc(void **p, size_t n, unsigned)
 {
     std::lock_guard<std::mutex> g(model().mu);
+    if (model().refuse) return hipErrorOutOfMemory;
     *p = malloc(n);
     model().pinned[static_cast<char *>(*p)] = n;
     model().pinned_bytes += n;

@@ -97,10 +97,11 @@ int main()
 """)
 
 
-def test_small_copies_open_no_more_than_the_area(tmp_path):
-    """Copies up to 256 KiB need the 1 MiB area and nothing else, larger ones
-    the chunks, events and helpers only from the sizes and the sum that pay for
-    them; every way moves the right bytes, and all of it is given back."""
+def test_copies_of_every_size(tmp_path):
+    """Copies of every size, many of them in one call among them, move the right
+    bytes in any order; the first 512 KiB of small ones need the area and nothing
+    else, more and larger ones the chunks, events and helpers, and all of it is
+    given back."""
     _run(tmp_path, HOSTCOPY + r"""
 #include <dirent.h>
 static int threads()
@@ -111,61 +112,120 @@ static int threads()
     closedir(d);
     return n;
 }
+constexpr size_t MiB = 1 << 20;
 int main()
 {
     Stream s;
-    const size_t most = 64 << 20;
+    const size_t most = 40 * MiB;
     const Bytes src = noise(most, 3);
-    Bytes dev(most), warm(most);
-    auto up = [&](HostCopy &h, size_t n) {
+    Bytes dev(most), out(most);
+    auto wait = [&](HostCopy &h) { expect(hipStreamSynchronize(&s) == hipSuccess, "wait"); h.settled(); };
+    auto up = [&](HostCopy &h, size_t n, size_t from = 0) {
         std::fill(dev.begin(), dev.begin() + n, 0);
-        expect(h.begin() == hipSuccess && h.put(0, dev.data(), src.data(), n, &s) == hipSuccess &&
-               hipStreamSynchronize(&s) == hipSuccess && std::equal(src.begin(), src.begin() + n, dev.begin()), "up");
-        h.settled();
+        h.begin();
+        expect(h.put(0, dev.data(), src.data() + from, n, &s) == hipSuccess, "put");
+        wait(h);
+        expect(std::equal(dev.begin(), dev.begin() + n, src.begin() + from), "up");
     };
-    auto down = [&](HostCopy &h, char *out, size_t n) {
-        expect(h.begin() == hipSuccess && h.get(0, out, dev.data(), n, &s) == hipSuccess && h.flush(&s) == hipSuccess &&
-               std::equal(out, out + n, dev.begin()), "down");
-    };
-    auto down_new = [&](HostCopy &h, size_t n) {
-        char *p = static_cast<char *>(mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0));
-        down(h, p, n);
-        munmap(p, n);
+    auto down = [&](HostCopy &h, size_t n) {
+        std::fill(out.begin(), out.begin() + n, 0);
+        h.begin();
+        expect(h.get(0, out.data(), dev.data(), n, &s) == hipSuccess && h.flush(&s) == hipSuccess &&
+               std::equal(out.begin(), out.begin() + n, dev.begin()), "down");
     };
     auto opened = [&](bool area, bool chunks) {
-        expect(model().pinned_bytes == (area ? HostCopy::kArea : 0) + (chunks ? HostCopy::kWorkers * HostCopy::kSlots * HostCopy::kChunk : 0) &&
-               model().events == (chunks ? int(HostCopy::kWorkers * HostCopy::kSlots) : 0) &&
-               threads() == (chunks ? int(HostCopy::kWorkers) : 1), "opened");
+        const size_t want = (area ? HostCopy::kArea : 0) + (chunks ? HostCopy::kWorkers * HostCopy::kSlots * HostCopy::kChunk : 0);
+        const bool ok = model().pinned_bytes == want && model().events == (chunks ? int(HostCopy::kWorkers * HostCopy::kSlots) : 0) &&
+                        threads() == (chunks ? int(HostCopy::kWorkers) : 1);
+        if (!ok) std::printf("area %d chunks %d: %zu bytes, %d events, %d threads\n", area, chunks, model().pinned_bytes,
+                             model().events, threads());
+        expect(ok, "opened");
     };
     {
         HostCopy h;
-        for (size_t n : {1u, 300u, 262144u, 262145u, 1048575u}) {
-            up(h, n);
-            down(h, warm.data(), n);
-            down_new(h, n);
-            opened(true, false);
+        for (size_t n : {1u, 300u, 4097u, 100000u}) {
+            up(h, n, n % 7);
+            down(h, n);
+        }
+        up(h, HostCopy::kOpenAfter - 2 * 104398);          // as much as does not open the chunks
+        opened(true, false);
+        up(h, 1);
+        opened(true, true);
+        for (size_t n : {262145u, 1048575u, 1048576u}) {
+            up(h, n, n % 7);
+            down(h, n);
         }
     }
     opened(false, false);
     {
+        // many copies in one call, with waits within
         HostCopy h;
-        up(h, most - 1);                           // uploads below 64 MiB, downloads into pages that are there below 4
-        for (int k = 0; k < 5; ++k) down(h, warm.data(), (4 << 20) - 1);
-        for (int k = 0; k < 7; ++k) down_new(h, 1 << 20);    // 7 MiB of those that gain
+        std::fill(dev.begin(), dev.end(), 0);
+        h.begin();
+        size_t at = 0;
+        for (int k = 0; k < 300; ++k) {
+            const size_t n = size_t(k) * 3700 % 200003 + 1;
+            expect(h.put(0, dev.data() + at, src.data() + at, n, &s) == hipSuccess, "put");
+            at += n;
+        }
+        wait(h);
+        expect(std::equal(dev.begin(), dev.begin() + at, src.begin()), "many up");
+        h.begin();
+        for (size_t x = 0, k = 0; x < at; ++k) {
+            const size_t n = std::min(at - x, (k * 7919) % (k % 3 ? 5003 : 300007) + 1);
+            expect(h.get(0, out.data() + x, dev.data() + x, n, &s) == hipSuccess, "get");
+            x += n;
+        }
+        expect(h.flush(&s) == hipSuccess && std::equal(out.begin(), out.begin() + at, src.begin()), "many down");
+    }
+    opened(false, false);
+    {
+        HostCopy h;
+        for (size_t n : {1048577u, 2097152u, 9000001u, 33554433u}) {
+            up(h, n, 11);
+            down(h, n);
+        }
+        opened(false, true);
+        // copies in chunks and small ones in one call
+        std::fill(dev.begin(), dev.end(), 0);
+        h.begin();
+        for (size_t at = 0, k = 0; at < most; ++k) {
+            const size_t n = std::min(most - at, k % 2 ? size_t(4097) : 3 * MiB + k);
+            expect(h.put(0, dev.data() + at, src.data() + at, n, &s) == hipSuccess, "put");
+            at += n;
+        }
+        wait(h);
+        expect(dev == src, "mixed up");
+        std::fill(out.begin(), out.end(), 0);
+        h.begin();
+        for (size_t at = 0, k = 0; at < most; ++k) {
+            const size_t n = std::min(most - at, k % 2 ? size_t(4097) : 3 * MiB + k);
+            expect(h.get(0, out.data() + at, dev.data() + at, n, &s) == hipSuccess, "get");
+            at += n;
+        }
+        expect(h.flush(&s) == hipSuccess && out == src, "mixed down");
+        opened(true, true);
+    }
+    opened(false, false);
+    {
+        // pinned memory of the caller's own, and none to be had for the copies
+        HostCopy h;
+        void *p = nullptr;
+        expect(hipHostMalloc(&p, 20 * MiB, 0) == hipSuccess, "pinned");
+        memcpy(p, src.data(), 20 * MiB);
+        std::fill(dev.begin(), dev.end(), 0);
+        h.begin();
+        expect(h.put(0, dev.data(), p, 20 * MiB, &s) == hipSuccess, "put");
+        wait(h);
+        expect(std::equal(dev.begin(), dev.begin() + 20 * MiB, src.begin()), "from pinned memory");
+        hipHostFree(p);
+        model().refuse = true;
+        up(h, 5);
+        up(h, 20 * MiB);
+        down(h, 20 * MiB);
+        down(h, 6);
+        model().refuse = false;
         opened(false, false);
-        down_new(h, 1 << 20);
-        opened(false, true);
-        for (size_t n : {1048576u, 1048577u, 2097152u, 4194304u, 9000001u}) {
-            down(h, warm.data(), n);
-            down_new(h, n);
-        }
-        opened(false, true);
-    }
-    opened(false, false);
-    {
-        HostCopy h;
-        up(h, most);
-        opened(false, true);
     }
     opened(false, false);
 }
