@@ -119,13 +119,6 @@ struct TraceArgs {
     uint32_t spread;                   // the waves it spreads a short one over,
     uint32_t slab;                     // the bytes of LDS of each,
     uint32_t already;                  // and the first pass's transitions
-    // Sorted survivors go to k_whole together where one in kJoinShare or more
-    // does not run in nodes and `join` lanes, one round of it, hold all of them
-    // (0: never): those few take a chain of it in any case, and beside them the
-    // rest takes no longer (plain-scale, 9,553 survivors of which 143 do not:
-    // 20,000 transitions 6.3 -> 2.9 ms; in slots 4.6).  fig1 and beaver, where
-    // none or few do not, stay in nodes.
-    uint32_t join;
     uint32_t *idx[9], *left[9];       // by list (left null: the budget less the first pass)
 };
 // Waves a block of k_trace (at most) and of k_whole.  One-wave blocks of a
@@ -229,11 +222,14 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
 // q->misfits and claimed through q->head_m; kListGeneral, kListEnd: that
 // list, rest_left its machines' transitions to go; a list of at most `few`
 // machines is left alone, or with a cap one of more)
-// the trace kernel over list ta.in
+// sorted survivors' lists into one, kListGeneral, where `join` lanes hold them
+// and some are there already
+hipError_t launch_join(const TraceArgs &ta, QueueState *q, uint32_t join, hipStream_t st);
 // whole memories in LDS, 2^sh lanes a wave, over list ta.in if it has at
 // most ta.few machines
 hipError_t launch_whole(const BatchTable *tab, uint32_t isa, bool pow2, bool wm, const TraceArgs &ta, uint32_t sh,
                         uint32_t blocks, QueueState *q, hipStream_t st);
+// the trace kernel over list ta.in
 hipError_t launch_trace(const BatchTable *tab, uint32_t already, uint32_t isa, bool wm, const TraceArgs &ta,
                         uint32_t wpb, uint32_t blocks, QueueState *q, hipStream_t st);
 // the persistent kernel over the fits of a hot-cell first pass, each

@@ -2146,12 +2146,34 @@ __device__ __forceinline__ gi32 *lane_of(gi32 *x, uint32_t src)
     return reinterpret_cast<gi32 *>(__shfl(reinterpret_cast<unsigned long long>(x), static_cast<int>(src)));
 }
 
-// sorted survivors go to k_whole together (TraceArgs::join; their counts stand
-// from the sorting on)
-__device__ __forceinline__ bool joined(const QueueState *q, uint32_t join)
+// Sorted survivors go to k_whole together where one in kJoinShare or more does
+// not run in nodes and `join` lanes, one round of it, hold all of them: those few
+// take a chain of it in any case, and beside them the rest takes no longer
+// (plain-scale, 9,553 survivors of which 143 do not: 20,000 transitions 6.3 ->
+// 3.3 ms; in slots 4.6).  fig1 and beaver, where none or few do not, stay in
+// nodes.  One block moves the lists' entries (in k_whole's own claim of several
+// lists the code around its loop took 10% of a transition).
+__global__ __launch_bounds__(1024) void k_join(TraceArgs ta, QueueState *q, uint32_t join)
 {
-    const unsigned long long g = q->count[kListGeneral], all = g + q->count[kListFull] + q->count[kListMain];
-    return g != 0 && kJoinShare * g >= all && all <= join;
+    const unsigned long long g = q->count[kListGeneral], f = q->count[kListFull], m = q->count[kListMain], all = g + f + m;
+    if (g == 0 || kJoinShare * g < all || all > join) return;
+    for (unsigned long long x = threadIdx.x; x < f + m; x += blockDim.x) {
+        const unsigned long long at = x < f ? x : x - f;
+        ta.idx[kListGeneral][g + x] = x < f ? ta.idx[kListFull][at] : ta.idx[kListMain][at];
+        ta.left[kListGeneral][g + x] = x < f ? ta.left[kListFull][at] : ta.left[kListMain][at];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        q->count[kListGeneral] = all;
+        q->count[kListFull] = 0;
+        q->count[kListMain] = 0;
+    }
+}
+
+hipError_t launch_join(const TraceArgs &ta, QueueState *q, uint32_t join, hipStream_t st)
+{
+    k_join<<<1, 1024, 0, st>>>(ta, q, join);
+    return hipGetLastError();
 }
 
 template <int ISA, bool WM>
@@ -2161,7 +2183,6 @@ __global__ __launch_bounds__(kWave * kTraceWpb) void k_trace(const BatchTable *_
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wib = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave)));
     const uint32_t wpb = blockDim.x / kWave;
-    if (joined(q, ta.join)) return;
     const uint64_t total = ta.in == kListFirst ? q->survivors : q->count[ta.in];
     unsigned long long *const head = ta.in == kListFirst ? &q->head : &q->next[ta.in];
     // few machines are spread over the launch's waves (a wave waits for every
@@ -2592,10 +2613,7 @@ __global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *_
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wib = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / kWave)));
     const uint32_t slab = wib * ta.slab;                 // the wave's LDS
-    // (joined: the list `in` is kListGeneral, the other two follow it)
-    const bool join = joined(q, ta.join);
-    const uint64_t own = ta.all != 0 ? ta.all : ta.in == kListFirst ? q->survivors : q->count[ta.in];
-    const uint64_t full = join ? q->count[kListFull] : 0u, total = own + full + (join ? q->count[kListMain] : 0u);
+    const uint64_t total = ta.all != 0 ? ta.all : ta.in == kListFirst ? q->survivors : q->count[ta.in];
     if (total > ta.few) return;
     unsigned long long *const head = ta.in == kListFirst ? &q->head : &q->next[ta.in];
     // as few lanes a wave as one wave a SIMD allows, then more lanes, then
@@ -2619,11 +2637,7 @@ __global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *_
         uint64_t v = 0;
         uint32_t left = 0, limit = 0, ws = 0, hw = 0;
         if (has) {
-            const bool in1 = item < own, in2 = item < own + full;
-            const uint64_t at = in1 ? item : in2 ? item - own : item - own - full;
-            const uint32_t *const idx = in1 ? ta.idx[ta.in] : in2 ? ta.idx[kListFull] : ta.idx[kListMain];
-            const uint32_t *const rest = in1 ? ta.left[ta.in] : in2 ? ta.left[kListFull] : ta.left[kListMain];
-            const uint32_t gid = ta.all != 0 ? static_cast<uint32_t>(item) : idx[at];
+            const uint32_t gid = ta.all != 0 ? static_cast<uint32_t>(item) : ta.idx[ta.in][item];
             const int k = batch_of(tab, gid);
             bp = &tab->b[k];
             v = gid - tab->start[k];
@@ -2636,7 +2650,7 @@ __global__ __launch_bounds__(kWave * kWholeWpb) void k_whole(const BatchTable *_
             T = gptr(bp->T + gany(bp->t_off)[v]);
             Y = gptr(bp->Y + gany(bp->y_off)[v]);
             const uint32_t budget = tab->budget[k];
-            left = limit = rest ? rest[at] : budget > ta.already ? budget - ta.already : 0u;
+            left = limit = ta.left[ta.in] ? ta.left[ta.in][item] : budget > ta.already ? budget - ta.already : 0u;
             has = left != 0 && gany(bp->status)[v] == 0;
             hw = ta.all != 0 ? min(gany(bp->hw)[v], r.n) : r.n;
         }

@@ -1162,21 +1162,18 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                     ta.rest = kListMain;
                     ta.stop = kTraceSort;
                     if (!e) e = traces(from, false, kListGeneral, kListFull, cus, st);
+                    if (!e) e = launch_join(ta, qs, round_w, st);
                     ta.stop = 0;
                     ta.events = kTraceEvents;
                     ta.fulls = kTraceFulls;
                     if (!e) e = hipEventRecord(c->ev_first, st);
                     if (!e) e = hipStreamWaitEvent(st2, c->ev_first, 0);
                     if (!e) e = hipStreamWaitEvent(st3, c->ev_first, 0);
-                    ta.join = round_w;
                     if (!e) e = timed_launch(c, RASP_KERNEL_MISFIT, [&] { return general(kListGeneral, st2); }, st2);
                     if (!e) e = hipEventRecord(c->ev_second, st2);
-                    const uint32_t join = ta.join;
                     ta.dense = kTraceDense;
                     if (!e) e = traces(kListFull, true, kListLast, kListLast, cus, st3);
-                    ta.join = 0;
                     if (!e) e = general(kListLast, st3);
-                    ta.join = join;
                     if (!e) e = hipEventRecord(c->ev_third, st3);
                     // (5/8 of the CUs hold 71,680 machines)
                     ta.dense = kWave;
@@ -1185,7 +1182,6 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                     ta.fulls = kLateFulls; ta.fulls_sh = kLateFullsSh;
                     if (!e) e = traces(kListMain, false, kListLate, kListLate, cus - cus / 8, st);
                     // (beside what still runs of the others' chains, not behind them)
-                    ta.join = 0;
                     if (!e) e = general(kListLate, st);
                     if (!e) e = hipStreamWaitEvent(st, c->ev_second, 0);
                     if (!e) e = hipStreamWaitEvent(st, c->ev_third, 0);
