@@ -217,11 +217,12 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
                              uint32_t lds_words, uint32_t max_n, uint32_t max_ell,
                              uint32_t waves_per_block, uint32_t blocks, uint32_t cap, uint32_t *surv,
                              QueueState *q, hipStream_t st, uint32_t which = 0,
-                             const uint32_t *rest_left = nullptr, uint32_t few = 0);
+                             const uint32_t *rest_left = nullptr, uint32_t few = 0, uint32_t cus = 0);
 // (which 1: the work list is a hot-cell first pass's misfit list, counted by
 // q->misfits and claimed through q->head_m; kListGeneral, kListEnd: that
 // list, rest_left its machines' transitions to go; a list of at most `few`
-// machines is left alone, or with a cap one of more)
+// machines is left alone, or with a cap one of more; cus: the compute units that
+// the waves of a list with memories in HBM are spread over)
 // sorted survivors' lists into one, kListGeneral, where `join` lanes hold them
 // and some are there already
 hipError_t launch_join(const TraceArgs &ta, QueueState *q, uint32_t join, hipStream_t st);

@@ -1354,8 +1354,22 @@ __device__ __forceinline__ void persistent_body(const BatchTable *__restrict__ t
     if (few != 0 && (cap == kNoCap ? total <= few : total > few)) return;
     // A claim takes up to 64 machines, so a short list leaves most waves
     // nothing to do but to queue up at its counter (8,192 waves and no machine:
-    // 115 us, 5 this way); four times those that find one stay in the race.
-    if (work != nullptr && 16ull * (static_cast<uint64_t>(blockIdx.x) * (blockDim.x / kWave) + wib) >= total) return;
+    // 115 us, 5 this way).  With memories in HBM (TL then holds the CUs) the
+    // waves that find machines are spread evenly: as many blocks on every CU,
+    // and of their waves, each block beginning with another, the same number.
+    // Where all raced for them some CUs had twice as many as others (65,536
+    // rollouts 138-150 or 157-202 ms, 122 this way).  Slots: four times the
+    // waves that can find one race.
+    if (work != nullptr) {
+        const uint32_t wpb = blockDim.x / kWave;
+        if (MODE == 0 && TL != 0) {
+            const uint64_t need = (total + kWave - 1u) / kWave, all = (need + static_cast<uint64_t>(TL) * wpb - 1u) / (static_cast<uint64_t>(TL) * wpb) * TL;
+            const uint32_t used = static_cast<uint32_t>(min(static_cast<uint64_t>(gridDim.x), all));
+            if (blockIdx.x >= used || static_cast<uint64_t>((wib + blockIdx.x / TL) % wpb) * used + blockIdx.x >= need) return;
+        } else if (16ull * (static_cast<uint64_t>(blockIdx.x) * wpb + wib) >= total) {
+            return;
+        }
+    }
 
     bool has = false, exhausted = false, fresh = false, cut = false;
     Regs r{};
@@ -2827,7 +2841,7 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
                              uint32_t already, uint32_t isa, bool pow2, bool wmb, uint32_t epoch,
                              uint32_t lds_words, uint32_t max_n, uint32_t max_ell,
                              uint32_t waves_per_block, uint32_t blocks, uint32_t cap, uint32_t *surv,
-                             QueueState *q, hipStream_t st, uint32_t which, const uint32_t *rest_left, uint32_t few)
+                             QueueState *q, hipStream_t st, uint32_t which, const uint32_t *rest_left, uint32_t few, uint32_t cus)
 {
     const uint32_t wm = wmb ? 1u : 0u;
     const dim3 grid(blocks), block(waves_per_block * kWave);
@@ -2840,12 +2854,12 @@ hipError_t launch_persistent(const BatchTable *tab, uint64_t total, const uint32
         if (mode == 1 && TL) return launch_k3_p<1, 1, true>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few);
         if (mode == 1) return launch_k3_p<1, 1, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
         if (mode == 2) return launch_k3_p<1, 2, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
-        return launch_k3_p<1, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
+        return launch_k3_p<1, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, cus, wm, cap, surv, q, which, rest_left, few);
     }
     if (mode == 1 && TL) return launch_k3_p<0, 1, true>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, TL, wm, cap, surv, q, which, rest_left, few);
     if (mode == 1) return launch_k3_p<0, 1, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
     if (mode == 2) return launch_k3_p<0, 2, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
-    return launch_k3_p<0, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, 0u, wm, cap, surv, q, which, rest_left, few);
+    return launch_k3_p<0, 0, false>(pow2, grid, block, shmem, st, tab, total, work, already, epoch, P, cus, wm, cap, surv, q, which, rest_left, few);
 }
 
 __global__ void k_zero_queue(QueueState *q, uint32_t head_only)

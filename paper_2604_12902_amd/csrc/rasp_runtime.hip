@@ -944,7 +944,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
         uint32_t few;
         const hipError_t e = whole(tb, wa, in, 1, &few, st);
         return e ? e : launch_persistent(tb, total, list, ran, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks, kNoCap,
-                                         nullptr, qs, st, in, nullptr, few);
+                                         nullptr, qs, st, in, nullptr, few, c->cus);
     };
     if (graphed) {
         // replay (capturing on first use) the launch sequence for this key
@@ -1057,7 +1057,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
         HIPCHK(c, hipStreamWaitEvent(st2, c->ev_first, 0));
         HIPCHK(c, timed_launch(c, RASP_KERNEL_MISFIT, [&] {
             return launch_persistent(dt2, total, ha.mis, cap, isa, pow2, wm, epoch, 0u, max_n, max_ell, 4u, blocks_m,
-                                     kNoCap, nullptr, qs, st2, 1u); }, st2));
+                                     kNoCap, nullptr, qs, st2, 1u, nullptr, 0u, c->cus); }, st2));
         HIPCHK(c, hipEventRecord(c->ev_second, st2));
         HIPCHK(c, timed_launch(c, RASP_KERNEL_PERSISTENT, [&] {
             return launch_persistent_hot(dt2, work, cap, isa, pow2, wm, epoch, ha, wpb_h, blocks_h, qs, st); }));
@@ -1137,7 +1137,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
             const uint32_t blocks_q = slots ? blocks : resident_blocks(c, 4u, 0u, waves);
             auto queue = [&](uint32_t in, uint32_t Pw, uint32_t wpbw, uint32_t blocksw, uint32_t few, hipStream_t on) {
                 return launch_persistent(dt2, total, ta.idx[in], ran, isa, pow2, wm, epoch, Pw, max_n, max_ell, wpbw, blocksw,
-                                         kNoCap, nullptr, qs, on, in, ta.left[in], few);
+                                         kNoCap, nullptr, qs, on, in, ta.left[in], few, cus);
             };
             // what does not run in nodes: memories whole in LDS if they are
             // few, else the work queue
@@ -1155,7 +1155,7 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 hipError_t e = hipSuccess;
                 if (warm)
                     e = launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
-                                          kTraceWarm - cap, ta.idx[kListWarm], qs, st);
+                                          kTraceWarm - cap, ta.idx[kListWarm], qs, st, kListFirst, nullptr, 0u, cus);
                 ta.events = sort ? kSortEvents : kTraceEvents; ta.events_sh = kTraceEventsSh;
                 ta.fulls = sort ? kSortFulls : kTraceFulls; ta.fulls_sh = kTraceFullsSh;
                 if (sort) {
@@ -1218,10 +1218,10 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 const uint32_t most = std::max(1u, 2 * round_w);
                 uint32_t *list = at<uint32_t>(c, c->trace);
                 hipError_t e = launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
-                                                 kTraceWarm - cap, list, qs, st, kListFirst, nullptr, most);
+                                                 kTraceWarm - cap, list, qs, st, kListFirst, nullptr, most, c->cus);
                 if (!e) e = survivors(dt2, list, kListWarm, kTraceWarm);
                 return e ? e : launch_persistent(dt2, total, work, cap, isa, pow2, wm, epoch, P, max_n, max_ell, wpb, blocks,
-                                                 kNoCap, nullptr, qs, st, kListFirst, nullptr, most); }));
+                                                 kNoCap, nullptr, qs, st, kListFirst, nullptr, most, c->cus); }));
         }
         for (uint32_t t = 0; t < k; ++t) bs[t]->dev.fresh = 0;
     } else if (cap >= maxb && !lds_first) {

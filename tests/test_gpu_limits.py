@@ -135,3 +135,17 @@ def test_work_queue_of_a_hot_cell_context(R, num_vms, n, lds_words):
         h = c.load(b)
         c.run(h, 8900)
         compare(c.fetch(h, mem=True), oracle.run(b, 8900, threads=8))
+
+
+# work lists with memories in HBM, of one machine to more waves than one block on
+# every compute unit holds: each machine is some wave's
+@pytest.mark.parametrize("num_vms", [1, 64, 65, 64 * 257, 64 * 4 * 256, 64 * 4 * 256 + 1, 64 * 4 * 300 + 7])
+def test_work_lists_of_every_length(R, num_vms):
+    print("case: work list", num_vms, flush=True)
+    n = 2049 if num_vms < 20000 else 1030
+    # (memories too large for k_whole, or more machines than it takes)
+    b = _mixed(num_vms, 3, n)
+    with _context(R, dict(first_pass=8)) as c:
+        h = c.load(b)
+        c.run(h, 150)
+        compare(c.fetch(h, digest=True), oracle.run(b, 150, threads=8), mem=False)

@@ -230,3 +230,24 @@ int main()
     opened(false, false);
 }
 """)
+
+
+def test_waves_of_a_work_list_are_spread_evenly():
+    """A model of which waves of a launch over a list with memories in HBM look for
+    machines: as many as find one (or all there are), and over compute units that
+    take blocks in turn, and over the places of a block's waves, as evenly as
+    whole blocks allow."""
+    import numpy as np
+    for cus in (1, 8, 64, 256):
+        for wpb in (1, 2, 4):
+            for per_cu in (1, 2, 4, 8):
+                grid = cus * per_cu
+                b, w = np.meshgrid(np.arange(grid), np.arange(wpb), indexing="ij")
+                for need in sorted({0, 1, 2, 3, cus, cus + 1, cus * wpb - 1, cus * wpb, cus * wpb + 1, 3 * cus + 7,
+                                    grid * wpb // 2, grid * wpb - 1, grid * wpb, grid * wpb + 9}):
+                    used = min(grid, -(-need // (cus * wpb)) * cus)
+                    on = (b < used) & (((w + b // cus) % wpb) * used + b < need)
+                    assert on.sum() == min(need, grid * wpb), (cus, wpb, per_cu, need)
+                    by_cu = np.bincount((b % cus)[on], minlength=cus)
+                    blocks = max(1, used // cus)
+                    assert by_cu.max() - by_cu.min() <= (blocks if need < used * wpb else 0), (cus, wpb, per_cu, need)
