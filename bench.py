@@ -787,7 +787,15 @@ def main():
             "kernel": dom, "kernel_ms": round(dom_ms, 4), "algorithmic_bytes": int(algo),
             "per_unit": unit_note,
             # the whole path: retired steps/s x algorithmic bytes per step against the peak
-            "path_frac": round(head["value"] * bstep / (HBM_PEAK_GBS * 1e9), 5)}
+            "path_frac": round(head["value"] * bstep / (HBM_PEAK_GBS * 1e9), 5),
+            # what these are shares of: the bytes a step touches wherever they lie
+            "basis": "algorithmic bytes at the HBM peak", "traffic_frac": None}
+    if traffic:
+        # where they lie in LDS the traffic measured is far less, and a step's
+        # dependence chain is the bound
+        roof["traffic_frac"] = round(traffic / (dom_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 5)
+        if roof["traffic_frac"] < 0.25:
+            roof["bound"] = "latency"
 
     cpu = None
     if not args.no_cpu_baseline:

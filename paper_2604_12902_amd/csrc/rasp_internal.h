@@ -131,17 +131,28 @@ constexpr uint32_t kTraceRounds = 16;  // general steps of a lane between runs o
 constexpr uint32_t kTraceNear = 32;    // macro steps before its end from which a lane waits for others,
 constexpr uint32_t kTraceEnd = 1;      // and from which its machine leaves
 // Sorted survivors run kTraceSort transitions first, transients among them,
-// which shows nearly all that do not run in small tables.
+// which shows nearly all that do not run in small tables.  Meanwhile kSortEvents
+// and kSortFulls stand for kTraceEvents and kTraceFulls (with those 24 and 2 at
+// once fig1's 262,144 machines take 15.37 ms, not 15.55, plain-scale with 20,000
+// transitions 3.26, not 3.39).
 constexpr uint32_t kTraceSort = 512;
-constexpr uint32_t kSortEvents = 64, kSortFulls = 4;         // as kTraceEvents and kTraceFulls, meanwhile
+constexpr uint32_t kSortEvents = 64, kSortFulls = 4;
 constexpr uint32_t kTraceEvents = 24, kTraceEventsSh = 11;   // general steps (and one in 2^Sh transitions) before a machine leaves
 constexpr uint32_t kTraceFulls = 2, kTraceFullsSh = 10;      // times its tables are full before it leaves
-constexpr uint32_t kLateEvents = 64, kLateEventsSh = 8;      // the same for kListLate
+// The same for kListLate, whose machines take a chain of k_whole from then on
+// (with kTraceEvents' and kTraceFulls' numbers fig1 and beaver are the same
+// within 1%, plain-scale 1-3% slower).
+constexpr uint32_t kLateEvents = 64, kLateEventsSh = 8;
 constexpr uint32_t kLateFulls = 16, kLateFullsSh = 9;
+// Sorted survivors go to k_whole together from one in kJoinShare on that has to
+// (k_join): plain-scale has one in 41, fig1 and beaver none in 2,800 and 67,000.
 constexpr uint32_t kJoinShare = 64;
 constexpr uint32_t kCrowdLeast = 8;    // machines of a wave from which on most of them may leave together,
-constexpr uint32_t kCrowdEvents = 8, kCrowdRate = 16;        // with 8 general steps and one in 16 transitions
-constexpr uint32_t kTraceDense = 4;                          // machines a wave of those beside the rest
+constexpr uint32_t kCrowdEvents = 8, kCrowdRate = 16;        // with 8 general steps and one in 16 transitions (4 steps: the same times)
+// Machines a wave of those beside the rest: few, since they compile often (fig1
+// in tables of 48 nodes 11.6 ms with 4, 19.9 with 8; in the pass as it is now 4
+// and 16 take 15.6 ms each).
+constexpr uint32_t kTraceDense = 4;
 constexpr uint32_t kTraceNodes = 16, kTraceData = 10;        // 7 waves a CU
 constexpr uint32_t kTraceNodes2 = 48, kTraceData2 = 40;      // 2 waves a CU
 // The largest memory traces are compiled for.  Positions would do to 2^15, but

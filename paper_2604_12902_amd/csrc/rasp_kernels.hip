@@ -1830,8 +1830,8 @@ hipError_t launch_persistent_hot(const BatchTable *tab, const uint32_t *work, ui
 // data and whose other instructions step in general.
 //
 // A machine that steps in general too often (uneven: 0.8% of the survivors,
-// plain-scale 4%: jumps and addresses computed anew on every round) leaves
-// for k_whole, one whose tables are too small (uneven 2%, fig1 1%) for a
+// plain-scale with 9,000 transitions and more 2%: jumps and addresses computed
+// anew on every round) leaves for k_whole, one whose tables are too small (uneven 2%, fig1 1%) for a
 // launch with larger ones, and one near the end of its budget for the work
 // queue, which takes its last few transitions at full occupancy.
 // The bound is a macro step's LDS round trip and the chain behind it (about

@@ -31,7 +31,9 @@ static_assert(sizeof(BatchTable) >= 8 * kMaxMulti * kTickets, "device count slot
 // not run in nodes, against 0.23-0.4 us a transition for all in lockstep.
 // Twelve served requests in epochs of 4,096 transitions: 2.1 ms an epoch with
 // traces, 1.7 without; 50,021 uneven machines with 16,320 left: 5.3 ms against
-// 6.8; plain-scale with 4,032 left: 1.9 against 1.4.
+// 6.8; plain-scale with 4,032 left: 1.9 against 1.4; 400,000 uneven machines
+// with 8,936 left 4.7-5.5 against 4.5, with 15,936 6.8-8.2 against 7.4; 262,144
+// of fig1 with 8,936 left 2.1 against 4.9.
 constexpr uint32_t kTraceMinLeft = 8192;
 // fewest for which transients go first where machines then run whole in LDS
 constexpr uint32_t kWarmMinLeft = 1024;
@@ -1104,7 +1106,8 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                 ta.idx[l] = at<uint32_t>(c, c->trace, part++ * list);
                 ta.left[l] = at<uint32_t>(c, c->trace, part++ * list);
             }
-            // Small memories: the survivors are sorted first, and what does not
+            // Small memories (k_whole then has room beside traces; 512 words lie
+            // between the populations measured): the survivors are sorted first, and what does not
             // run in small tables runs beside the rest, on the CUs its launch
             // leaves (fig1: 14.2 ms beside 11.1 and 10.4, one after the other
             // 25.9 -> 15.9 ms a pass; beaver, with few such machines, 7.5
@@ -1175,7 +1178,11 @@ int run_batches(rasp_ctx *c, Batch **bs, const uint32_t *budgets, uint32_t k, co
                     if (!e) e = traces(kListFull, true, kListLast, kListLast, cus, st3);
                     if (!e) e = general(kListLast, st3);
                     if (!e) e = hipEventRecord(c->ev_third, st3);
-                    // (5/8 of the CUs hold 71,680 machines)
+                    // The main launch takes 5/8 of the CUs at least (they hold
+                    // 71,680 machines) and leaves 1/8 to the lists beside it:
+                    // spread over all, fig1's 66,308 machines leave those no
+                    // room (25.4 ms against 20.0); on all but as few as they
+                    // need it makes no difference (19.7).
                     ta.dense = kWave;
                     ta.least = cus * 5 / 8;
                     ta.events = kLateEvents; ta.events_sh = kLateEventsSh;
